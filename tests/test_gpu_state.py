@@ -1,0 +1,81 @@
+"""The matrix-core chunk-state kernel behind kata_prefill_state, at the edges of
+its tiles: widths that do and do not split into 16-byte pieces, every value
+width class (up to 32, 64, 128, 256 columns), few and many tiles (one wave or
+four per tile), token counts around the staged block, and the overflow route."""
+import numpy as np
+import pytest
+
+from gpu_helpers import log
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24  # unit roundoff of fp32
+
+
+@pytest.fixture(scope="module")
+def kata():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2607_17419_amd as k
+    k.lib()  # raises if libkata.so is missing: no fallback
+    return k
+
+
+def _pairs(d, g):
+    m = d // g
+    a, b = np.triu_indices(m)
+    return (np.concatenate([a + i * m for i in range(g)]),
+            np.concatenate([b + i * m for i in range(g)]))
+
+
+def _inputs(dtype, H, T, d, dv, seed):
+    import torch
+    gen = torch.Generator().manual_seed(seed)
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    return (torch.randn((1, H, T, d), generator=gen).to(tt),
+            torch.randn((1, H, T, dv), generator=gen).to(tt))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H,T,d,dv,g", [
+    (1, 1, 64, 64, 1), (2, 63, 64, 64, 1), (2, 65, 64, 64, 2), (3, 128, 32, 32, 1),
+    (2, 100, 7, 5, 1), (2, 129, 24, 40, 3), (1, 70, 64, 256, 1), (1, 64, 40, 129, 1),
+    (8, 65, 64, 64, 1), (40, 33, 33, 66, 1)])
+def test_state_edges(kata, dtype, H, T, d, dv, g):
+    import torch
+    log(f"case state {dtype} H{H} T{T} d{d} dv{dv} g{g}")
+    k, v = _inputs(dtype, H, T, d, dv, 7)
+    S, z = kata.mg_prefill_state(k.cuda(), v.cuda(), g)
+    torch.cuda.synchronize()
+    a, b = _pairs(d, g)
+    k64, v64 = k.double().numpy()[0], v.double().numpy()[0]
+    phi = k64[:, :, a] * k64[:, :, b]
+    # fp32 products and sums in any order: each of the T terms passes at most
+    # T + 1 additions and two product roundings
+    tol = (T + 3) * U
+    for got, ref, mag in (
+            (S, np.einsum("htf,htj->hfj", phi, v64),
+             np.einsum("htf,htj->hfj", np.abs(phi), np.abs(v64))),
+            (z, phi.sum(1), np.abs(phi).sum(1))):
+        err = np.abs(got.cpu().numpy()[0].astype(np.float64) - ref)
+        assert np.all(err <= tol * mag + 1e-37), (err / np.maximum(mag, 1e-30)).max()
+
+
+def test_state_overflow_matches_fp32(kata):
+    """A product k_a k_b past fp32's range gives the infinities (and no NaN)
+    that fp32 arithmetic gives, and leaves the other features alone."""
+    import torch
+    k, v = _inputs("bf16", 2, 70, 64, 64, 8)
+    k[0, 1, 5, 3] = 3e25
+    S, z = kata.prefill_state(k.cuda(), v.cuda())
+    torch.cuda.synchronize()
+    a, b = _pairs(64, 1)
+    kf, vf = k.float()[0], v.float()[0]
+    ref = torch.matmul((kf[:, :, a] * kf[:, :, b]).transpose(1, 2).contiguous(), vf)
+    got = S.cpu()[0]
+    assert int(torch.isinf(ref).sum()) == 64
+    assert torch.equal(torch.isinf(got), torch.isinf(ref))
+    assert not torch.isnan(got).any() and torch.isinf(z.cpu()[0, 1]).sum() == 1
+    fin = torch.isfinite(ref)
+    assert torch.allclose(got[fin], ref[fin], rtol=1e-4, atol=1e-4)
