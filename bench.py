@@ -668,16 +668,26 @@ def bench_backward(kata, dev, hip, Ts=(1024, 2048, 4096, 8192), steps=5, warmup=
                 r["mfma_bf16"] = {"achieved": round(tf, 1), "peak": PEAK_BF16_TFLOPS,
                                   "unit": "TFLOP/s", "frac": round(tf / PEAK_BF16_TFLOPS, 4)}
             return r
+        # up to T = 4096 (8192 from eight heads on) the backward forms no chunk
+        # states: its state and scan intervals are empty, and its gradients are
+        # five 64-wide products per causal pair on the matrix cores
+        quadratic = T <= 4096 or (T <= 8192 and B * H >= 8)
         row = {"T": T, "inputs": src, "train_step_ms": round(ms, 3),
                "forward_ms": round(fwd_ms, 3), "backward_ms": round(sum(st.values()), 3),
-               "tokens_per_s": B * T / (ms * 1e-3),
-               "state_and_scan_fused": fused, "forward_saves_denominators": True,
-               "backward_stages_ms": {nm: round(t, 4) for nm, t in st.items()},
-               "gradients_roofline": hbm_rate(by["gradients"], st["gradients"], fl["grad"]),
-               "bwd_states_roofline": hbm_rate(by["bwd_states"], st["bwd_states"], fl["state"]),
-               "fwd_states_roofline": hbm_rate(by["fwd_states"], st["fwd_states"], fl["state"])}
-        if not fused:
-            row["suffix_scan_roofline"] = hbm_rate(by["scan"], st["suffix_scan"])
+               "tokens_per_s": B * T / (ms * 1e-3), "quadratic_backward": quadratic,
+               "state_and_scan_fused": fused and not quadratic, "forward_saves_denominators": True,
+               "backward_stages_ms": {nm: round(t, 4) for nm, t in st.items()}}
+        if quadratic:
+            tf = B * H * T * (T + 1) * 5 * d / (st["gradients"] * 1e-3) / 1e12
+            row["gradients_roofline"] = {"bound": "mfma_bf16", "achieved": round(tf, 1),
+                                         "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                                         "frac": round(tf / PEAK_BF16_TFLOPS, 4)}
+        else:
+            row["gradients_roofline"] = hbm_rate(by["gradients"], st["gradients"], fl["grad"])
+            row["bwd_states_roofline"] = hbm_rate(by["bwd_states"], st["bwd_states"], fl["state"])
+            row["fwd_states_roofline"] = hbm_rate(by["fwd_states"], st["fwd_states"], fl["state"])
+            if not fused:
+                row["suffix_scan_roofline"] = hbm_rate(by["scan"], st["suffix_scan"])
         row["paper_linear_state_m1_train_step_h100_ms"] = PAPER_TRAIN_STEP_H100.get(T)
         rows.append(row)
         del fws, bws, out, grads, q, k, v, dout

@@ -341,14 +341,17 @@ KATA_API int kata_lin_default_span(int B, int H, int T, int d, int dv, int C,
  *   bf16, z fp32, fp32 sums) and the gradient products run on the bf16 matrix
  *   cores with fp32 accumulation, a_t and b_t entering as bf16 hi + lo pairs;
  *   that path's gradients are within 2e-2 (per-head relative l2) of the exact
- *   ones, about 2e-3 on the test workloads.
+ *   ones, about 2e-3 on the test workloads.  Up to T = 4096 (8192 from eight
+ *   heads B x H on) those shapes take the quadratic form instead, pair tiles on
+ *   the same matrix cores with no chunk states (a_t as a bf16 pair, b_t fp32).
  *   workspace : >= kata_bwd_workspace_bytes(...) bytes, 256-byte aligned,
  *   caller-owned, contents undefined on exit; kata_bwd_chunked allocates it
  *   stream-ordered.  stage_events : 7 caller-created events, recorded before
  *   the first launch and after each of the six (forward states, prefix scan,
  *   per-token coefficients, backward states, suffix scan, gradients); where
  *   kata_bwd_fused_scan() is 1 each state launch also writes the scanned
- *   records and the two scan intervals are empty.
+ *   records and the two scan intervals are empty; the quadratic form leaves
+ *   all four state and scan intervals empty.
  */
 KATA_API kata_status_t kata_bwd_chunked(const void* q, const void* k, const void* v,
                                         const float* out, const float* dout, float* dq,
@@ -384,8 +387,9 @@ KATA_API kata_status_t kata_bwd_chunked_ex(const void* q, const void* k, const v
                                            hipStream_t stream);
 KATA_API size_t kata_bwd_workspace_bytes(int B, int H, int T, int d, int dv, int C, int g,
                                          kata_dtype_t dtype);
-/* 1 when kata_bwd_chunked* computes the prefix and suffix records of this
- * shape with the state and the scan in one launch each (bf16 inputs at
+/* The form of the chunk-state backward for this shape (whether or not its T
+ * takes the quadratic form): 1 when it computes the prefix and suffix records
+ * with the state and the scan in one launch each (bf16 inputs at
  * d = dv = C = 64, g = 1, from 16 heads B x H on), 0 when it runs a state launch
  * and a scan launch for each, -1 for an unsupported shape. */
 KATA_API int kata_bwd_fused_scan(int B, int H, int T, int d, int dv, int C, int g,

@@ -923,6 +923,8 @@ hipError_t launch_bwd(const void* q, const void* k, const void* v, const float* 
   // (the C ABI has checked that every tensor is 16-byte aligned)
   bool bf = false;
   if constexpr (std::is_same<Tin, bf16_t>::value) bf = bwd_bf_ok(d, dv, C, g);
+  if (bf && bwd_quad_ok(BH, T))
+    return launch_bwd_quad(q, k, v, out, dout, den, dq, dk, dv_out, BH, T, ws, st, ev);
   // bf16 path: from bwd_bf_fused_min_heads() heads on, each state launch also
   // scans (one pass, sequential over a head's chunks); with fewer heads the
   // chunk-parallel state launch and the record scan are faster

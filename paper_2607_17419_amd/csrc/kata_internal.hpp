@@ -97,6 +97,13 @@ hipError_t launch_bwd_prefix_bf(bool backward, const void* x, const void* y, voi
 hipError_t launch_bwd_grad_bf(const void* q, const void* k, const void* v, const float* ab,
                               const void* frec, const void* brec, float* dq, float* dk,
                               float* dv_out, int BH, int T, hipStream_t st);
+// Gradients in the quadratic (flash-style) form (kata_bwd_quad.hip), for the
+// shapes of bwd_bf_ok(); forms no records and uses 264 bytes of workspace per
+// token.  ev as for launch_bwd (the record intervals are empty).
+bool bwd_quad_ok(int BH, int T);
+hipError_t launch_bwd_quad(const void* q, const void* k, const void* v, const float* out,
+                           const float* dout, const float* den, float* dq, float* dk,
+                           float* dv_out, int BH, int T, void* ws, hipStream_t st, hipEvent_t* ev);
 size_t bwd_workspace(int BH, int T, int d, int dv, int C, int g);
 // ev: null, or 7 events recorded before the first kernel and after each of the
 // six launches (forward states, prefix scan, coefficients, backward states,
