@@ -70,7 +70,9 @@ typedef enum { KATA_F32 = 0, KATA_BF16 = 1 } kata_dtype_t;
  *   B, H, T >= 1.  d in 1..64.  dv >= 1.  C >= 1 is the chunk size.
  *   Fast path (bf16 MFMA): dtype = KATA_BF16, d in {32, 64}, dv = 64,
  *   C a multiple of 32 up to 1024.  Every other shape with d <= 64, dv <= 256
- *   and C <= 128 runs on the fp32 path; anything else is KATA_ERR_UNSUPPORTED.
+ *   and C <= 128 runs on the fp32 path (up to a length that grows with d in the
+ *   quadratic form, which needs none of its workspace); anything else is
+ *   KATA_ERR_UNSUPPORTED.
  *   Workspace (kata_fwd_workspace_bytes) is allocated stream-ordered with
  *   hipMallocAsync on `stream` and released with hipFreeAsync.
  */
@@ -343,7 +345,9 @@ KATA_API int kata_lin_default_span(int B, int H, int T, int d, int dv, int C,
  *   that path's gradients are within 2e-2 (per-head relative l2) of the exact
  *   ones, about 2e-3 on the test workloads.  Up to T = 4096 (8192 from eight
  *   heads B x H on) those shapes take the quadratic form instead, pair tiles on
- *   the same matrix cores with no chunk states (a_t as a bf16 pair, b_t fp32).
+ *   the same matrix cores with no chunk states (a_t as a bf16 pair, b_t fp32),
+ *   and so do the fp32-arithmetic shapes with g = 1 and dv <= 64 up to T = 4096
+ *   (8192 where d and dv are 16, 32 or 64), in fp32.
  *   workspace : >= kata_bwd_workspace_bytes(...) bytes, 256-byte aligned,
  *   caller-owned, contents undefined on exit; kata_bwd_chunked allocates it
  *   stream-ordered.  stage_events : 7 caller-created events, recorded before

@@ -554,6 +554,12 @@ hipError_t launch_fp32_forward(const void* q, const void* k, const void* v, floa
   const long long bh_stride = rec * NC;
   hipError_t e = record(ev, 0, st);
   if (e != hipSuccess) return e;
+  if (quad32_fwd_ok(BH, T, d, g)) {  // one launch, no states
+    for (int i = 1; i < 3; ++i)
+      if ((e = record(ev, i, st)) != hipSuccess) return e;
+    if ((e = launch_quad32_fwd<Tin>(q, k, v, out, BH, T, d, dv, st)) != hipSuccess) return e;
+    return record(ev, 3, st);
+  }
   launch_chunk_state<Tin>(k, v, states, states + static_cast<long long>(n) * dv, BH, T, d, dv, C,
                           NC, g, bh_stride, rec, bh_stride, rec, st);
   if ((e = record(ev, 1, st)) != hipSuccess) return e;

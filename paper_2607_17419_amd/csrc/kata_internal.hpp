@@ -37,6 +37,20 @@ template <typename Tin>
 hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const void* v,
                          float* out, int BH, int d, int dv, int g, hipStream_t st);
 
+// ---- quadratic form in fp32 (kata_quad32.hip) -------------------------------
+// g = 1; d <= 64, dv <= 256 (gradients: dv <= 64).  The gradients use dv + 1
+// floats of workspace per token and two per head; ev as for launch_bwd.
+bool quad32_fwd_ok(int BH, int T, int d, int g);
+bool quad32_bwd_ok(int BH, int T, int d, int dv, int g);
+template <typename Tin>
+hipError_t launch_quad32_fwd(const void* q, const void* k, const void* v, float* out, int BH,
+                             int T, int d, int dv, hipStream_t st);
+template <typename Tin>
+hipError_t launch_quad32_bwd(const void* q, const void* k, const void* v, const float* out,
+                             const float* dout, const float* den, float* dq, float* dk,
+                             float* dv_out, int BH, int T, int d, int dv, void* ws,
+                             hipStream_t st, hipEvent_t* ev);
+
 // ---- bf16 MFMA path (kata_mfma.hip) ---------------------------------------
 // g: feature blocks of KATA-Mg (1 or, at d = 64, 2)
 bool mfma_supported(int d, int dv, int C, int g);

@@ -1,0 +1,119 @@
+"""The fp32 quadratic form behind the fp32 forward and backward (one feature
+block): widths that do and do not fill their 16 / 32 / 64 (128, 256) classes, T
+around the 32-row tiles and the eight waves' shares of the walk, fp32 and bf16
+inputs, rows with a zero denominator, and the lengths where the chunk states
+take over."""
+import numpy as np
+import pytest
+
+from gpu_helpers import log
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24  # unit roundoff of fp32
+
+
+@pytest.fixture(scope="module")
+def kata():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2607_17419_amd as k
+    k.lib()  # raises if libkata.so is missing: no fallback
+    return k
+
+
+def _inputs(dtype, B, H, T, d, dv, seed=11):
+    import torch
+    gen = torch.Generator().manual_seed(seed)
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    def unit(x):
+        return x / x.norm(dim=-1, keepdim=True)
+    q, k = (unit(torch.randn((B, H, T, d), generator=gen)).to(tt) for _ in range(2))
+    v = torch.randn((B, H, T, dv), generator=gen).to(tt)
+    return q, k, v, torch.randn((B, H, T, dv), generator=gen)
+
+
+def _dense(q, k, v, dout):
+    """Outputs, gradients and, for each, the sums of their terms' magnitudes."""
+    q, k, v, g = (x.double().numpy() for x in (q, k, v, dout))
+    s = np.tril(np.matmul(q, k.swapaxes(-1, -2)))
+    w = s * s
+    D = w.sum(-1, keepdims=True)
+    inv = np.divide(1.0, D, out=np.zeros_like(D), where=D > 0)
+    o = np.matmul(w, v) * inv
+    a = g * inv
+    c = np.tril(np.matmul(a, v.swapaxes(-1, -2)) - (a * o).sum(-1, keepdims=True)) * s
+    ab = np.abs
+    cm = np.tril(np.matmul(ab(a), ab(v).swapaxes(-1, -2)) + (ab(a) * ab(o)).sum(-1, keepdims=True))
+    sm = np.tril(np.matmul(ab(q), ab(k).swapaxes(-1, -2)))
+    tr = lambda x: x.swapaxes(-1, -2)
+    vals = (o, 2 * np.matmul(c, k), 2 * np.matmul(tr(c), q), np.matmul(tr(w), a))
+    mags = (np.matmul(sm * sm, ab(v)) * inv, 2 * np.matmul(cm * sm, ab(k)),
+            2 * np.matmul(tr(cm * sm), ab(q)), np.matmul(tr(sm * sm), ab(a)))
+    return vals, mags
+
+
+# fp32 rounding of a term: its products and the sums of d, dv or T values that
+# it passes, in the scores (twice), D, a_t and the result; the sums run over
+# at most T / 8 + 8 values one after the other, so (4 (d + dv) + T) roundoffs
+# bound every output with room to spare, and each is far below it in practice
+def _tol(T, d, dv):
+    return (4 * (d + dv) + T + 16) * U
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,T,d,dv,C", [
+    (1, 1, 1, 16, 16, 32), (1, 2, 31, 7, 5, 16), (2, 4, 33, 16, 64, 32), (1, 3, 64, 32, 16, 64),
+    (1, 2, 65, 33, 30, 64), (1, 8, 256, 64, 33, 24), (1, 2, 257, 24, 40, 32), (3, 3, 300, 48, 64, 48)])
+def test_forward_and_gradients(kata, dtype, B, H, T, d, dv, C):
+    import torch
+    log(f"case fp32 quadratic {dtype} B{B} H{H} T{T} d{d} dv{dv} C{C}")
+    q, k, v, g = _inputs(dtype, B, H, T, d, dv)
+    if T > 40:
+        q[:, :, [3, 32, 40]] = 0  # zero denominators
+    vals, mags = _dense(q, k, v, g)
+    qd, kd, vd, gd = (x.cuda() for x in (q, k, v, g))
+    out = kata.fwd_chunked(qd, kd, vd, C)
+    exact = torch.from_numpy(vals[0].astype(np.float32)).cuda()
+    got = (out,) + tuple(kata.bwd_chunked(qd, kd, vd, exact, gd, C))
+    torch.cuda.synchronize()
+    for name, x, ref, mag in zip(("o", "dq", "dk", "dv"), got, vals, mags):
+        err = np.abs(x.double().cpu().numpy() - ref)
+        worst = (err / np.maximum(mag, 1e-30)).max()
+        log(f"  {name}: worst error {worst / U:.1f} roundoffs of the magnitude sum")
+        assert np.all(err <= _tol(T, d, dv) * mag + 1e-30), name
+    if T > 40:
+        assert not got[0][:, :, [3, 32, 40]].any() and not got[1][:, :, [3, 32, 40]].any()
+
+
+@pytest.mark.parametrize("dv", [66, 128, 130, 256])
+def test_wide_values(kata, dv):
+    import torch
+    log(f"case fp32 quadratic forward B1 H2 T100 d64 dv{dv}")
+    q, k, v, g = _inputs("f32", 1, 2, 100, 64, dv)
+    vals, mags = _dense(q, k, v, g)
+    out = kata.fwd_chunked(q.cuda(), k.cuda(), v.cuda(), 64)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(out.double().cpu().numpy() - vals[0]) <= _tol(100, 64, dv) * mags[0] + 1e-30)
+
+
+@pytest.mark.parametrize("d,dv,T", [(7, 5, 4096), (16, 16, 8192)])
+def test_against_chunk_states(kata, d, dv, T):
+    """T + 40 tokens run through the chunk states, T in the quadratic form: the
+    same first T outputs; and the gradients of a cotangent that is zero past T,
+    given the same forward output, are the same too."""
+    import torch
+    log(f"case fp32 quadratic against chunk states B1 H2 T{T} d{d} dv{dv}")
+    q, k, v, g = (x.cuda() for x in _inputs("f32", 1, 2, T + 40, d, dv))
+    g[:, :, T:] = 0
+    cut = lambda x: x[:, :, :T].contiguous()
+    long = kata.fwd_chunked(q, k, v, 32)
+    short = kata.fwd_chunked(cut(q), cut(k), cut(v), 32)
+    assert float((long[:, :, :T] - short).abs().max()) <= 2e-5 * float(long.abs().max())
+    a = kata.bwd_chunked(q, k, v, long, g, 32)
+    b = kata.bwd_chunked(cut(q), cut(k), cut(v), cut(long), cut(g), 32)
+    torch.cuda.synchronize()
+    for name, x, y in zip(("dq", "dk", "dv"), a, b):
+        assert float((cut(x) - y).norm() / y.norm()) <= 2e-5, name
+        assert not x[:, :, T:].any() or name == "dq"
