@@ -109,7 +109,9 @@ KATA_API size_t kata_noalloc_scratch_bytes(void);
  *   span_chunks : number of chunks folded into one stored state (the state
  *                 written to HBM covers span_chunks*C tokens; the chunks inside
  *                 a span are combined on chip).  0 selects the default
- *                 (kata_fwd_default_span).  1 is the per-chunk form.  Results do
+ *                 (kata_fwd_default_span; on the fast path, sequences short
+ *                 enough for it to be the faster form are evaluated
+ *                 quadratically, with no stored state).  1 is the per-chunk form.  Results do
  *                 not depend on it beyond rounding.
  *   workspace   : device buffer of at least kata_fwd_workspace_bytes(...)
  *                 bytes, 256-byte aligned, owned by the caller, contents
@@ -125,7 +127,7 @@ KATA_API kata_status_t kata_fwd_chunked_ws(const void* q, const void* k, const v
  * kata_fwd_chunked_ws plus stage timing, for profiling: stage_events[0..3]
  * (caller-created HIP events, all non-null) are recorded on `stream` before the
  * state kernel and after each of the three stages (chunk or span state,
- * associative scan, output).  Nothing synchronises; the caller reads the
+ * associative scan, output; the first two are empty in the quadratic form).  Nothing synchronises; the caller reads the
  * elapsed times with hipEventElapsedTime once the stream has reached them.
  */
 KATA_API kata_status_t kata_fwd_chunked_timed(const void* q, const void* k, const void* v,
@@ -169,8 +171,8 @@ KATA_API int kata_fwd_default_span(int B, int H, int T, int d, int dv, int C, ka
  *   Supported: dtype = KATA_BF16, d in {32, 64}, dv = 64 (bf16 MFMA);
  *   other valid arguments give KATA_ERR_UNSUPPORTED.  B*H <= 65535.
  *   workspace : device buffer of at least kata_fwd_quadratic_workspace_bytes(...)
- *               bytes, 256-byte aligned, caller-owned (it receives a permuted
- *               bf16 copy of V^T), contents undefined on exit.
+ *               bytes, 256-byte aligned, caller-owned (checked, but unused since
+ *               no copy of V is made any more).
  * kata_fwd_quadratic allocates that workspace stream-ordered (hipMallocAsync /
  * hipFreeAsync on `stream`).
  */

@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkata.so")
 SOURCES = ["kata_api.hip", "kata_fp32.hip", "kata_mfma.hip", "kata_linear.hip", "kata_bwd.hip",
-           "kata_bwd_bf.hip", "kata_bwd_quad.hip", "kata_quad32.hip"]
+           "kata_bwd_bf.hip"]
 # per-source flags: the bf16 gradients kernel updates MFMA results with VALU code,
 # so its MFMAs write VGPRs (no AGPR copies)
 EXTRA = {"kata_bwd_bf.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}

@@ -105,6 +105,17 @@ size_t fwd_workspace_bytes(int B, int H, int T, int d, int dv, int C, int dtype,
   return workspace_for(p, B, H, T, d, dv, C, g, span_chunks);
 }
 
+// The quadratic form in place of the span pipeline: the state and scan stages
+// are empty.
+hipError_t quad_staged(const void* q, const void* k, const void* v, float* out, float* den, int BH,
+                       int T, int d, int g, hipStream_t stream, hipEvent_t* ev) {
+  hipError_t e;
+  for (int i = 0; i < 3; ++i)
+    if ((e = kata::record(ev, i, stream)) != hipSuccess) return e;
+  if ((e = kata::launch_quad_fwd(q, k, v, out, den, BH, T, d, g, stream)) != hipSuccess) return e;
+  return kata::record(ev, 3, stream);
+}
+
 // den: null, or where the MFMA path writes the denominators D_t (fp32 [B][H][T])
 kata_status_t fwd_ws(const void* q, const void* k, const void* v, float* out, int B, int H,
                      int T, int d, int dv, int C, int g, kata_dtype_t dtype, int span_chunks,
@@ -117,6 +128,7 @@ kata_status_t fwd_ws(const void* q, const void* k, const void* v, float* out, in
   const Path p = fwd_path(B, H, T, d, dv, C, dtype, g);
   if (p == Path::kInvalid) return KATA_ERR_INVALID_ARG;
   if (p == Path::kUnsupported) return KATA_ERR_UNSUPPORTED;
+  const bool by_default = span_chunks == 0;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return KATA_ERR_INVALID_ARG;
   if (span_chunks == 0) span_chunks = default_span(C, d, p);
   if (p == Path::kFp32) span_chunks = 1;
@@ -124,6 +136,8 @@ kata_status_t fwd_ws(const void* q, const void* k, const void* v, float* out, in
   if (workspace_bytes < need) return KATA_ERR_INVALID_ARG;
   const int BH = B * H;
   if (p == Path::kMfma) {
+    if (by_default && kata::quad_fwd_ok(BH, T, d, g))
+      return from_hip(quad_staged(q, k, v, out, den, BH, T, d, g, stream, ev));
     const int L = span_tokens(T, C, span_chunks);
     if ((static_cast<long long>(T) + L - 1) / L > kGridYZ) return KATA_ERR_UNSUPPORTED;
     return from_hip(kata::launch_mfma_forward(q, k, v, out, den, BH, T, d, dv, g, L, workspace,
@@ -161,7 +175,7 @@ kata_status_t fwd_alloc(const void* q, const void* k, const void* v, float* out,
   void* ws = nullptr;
   if (alloc_ws(&ws, bytes, stream) != KATA_OK) return KATA_ERR_HIP;
   const kata_status_t st =
-      fwd_ws(q, k, v, out, B, H, T, d, dv, C, g, dtype, span, ws, bytes, nullptr, stream);
+      fwd_ws(q, k, v, out, B, H, T, d, dv, C, g, dtype, 0, ws, bytes, nullptr, stream);
   const hipError_t fe = hipFreeAsync(ws, stream);
   if (st != KATA_OK) return st;
   return from_hip(fe);
@@ -229,11 +243,18 @@ kata_status_t fwd_noalloc(const void* q, const void* k, const void* v, float* ou
   void* ws = nullptr;
   const kata_status_t st = scratch_ptr(stream, &ws);
   if (st != KATA_OK) return st;
-  return fwd_ws(q, k, v, out, B, H, T, d, dv, C, g, dtype, span, ws, kNoAllocScratchBytes,
-                nullptr, stream);
+  return fwd_ws(q, k, v, out, B, H, T, d, dv, C, g, dtype, 0, ws, kNoAllocScratchBytes, nullptr,
+                stream);
 }
 
-// Quadratic form: bf16 MFMA path only.
+// Quadratic form: bf16 MFMA path only.  It uses no workspace; its calls still
+// ask for, check and allocate the size that the ABI has always had (a bf16 copy
+// of V rounded up to 128 keys), so that what they refuse stays the same.
+size_t quad_workspace(int BH, int T, int dv) {
+  const size_t keys = (static_cast<size_t>(T) + 127) / 128 * 128;
+  return (static_cast<size_t>(BH) * dv * keys * sizeof(uint16_t) + 255) & ~static_cast<size_t>(255);
+}
+
 kata_status_t quad_check(int B, int H, int T, int d, int dv, int dtype, int g) {
   if (B < 1 || H < 1 || T < 1 || d < 1 || dv < 1) return KATA_ERR_INVALID_ARG;
   if (dtype != KATA_F32 && dtype != KATA_BF16) return KATA_ERR_INVALID_ARG;
@@ -246,7 +267,7 @@ kata_status_t quad_check(int B, int H, int T, int d, int dv, int dtype, int g) {
 
 size_t quad_workspace_bytes(int B, int H, int T, int d, int dv, int dtype, int g) {
   if (quad_check(B, H, T, d, dv, dtype, g) != KATA_OK) return 0;
-  return kata::mfma_quadratic_workspace(B * H, T, dv);
+  return quad_workspace(B * H, T, dv);
 }
 
 kata_status_t quad_ws(const void* q, const void* k, const void* v, float* out, int B, int H,
@@ -257,9 +278,8 @@ kata_status_t quad_ws(const void* q, const void* k, const void* v, float* out, i
   const kata_status_t c = quad_check(B, H, T, d, dv, dtype, g);
   if (c != KATA_OK) return c;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return KATA_ERR_INVALID_ARG;
-  if (workspace_bytes < kata::mfma_quadratic_workspace(B * H, T, dv)) return KATA_ERR_INVALID_ARG;
-  return from_hip(
-      kata::launch_mfma_quadratic(q, k, v, out, B * H, T, d, dv, g, workspace, stream));
+  if (workspace_bytes < quad_workspace(B * H, T, dv)) return KATA_ERR_INVALID_ARG;
+  return from_hip(kata::launch_quad_fwd(q, k, v, out, nullptr, B * H, T, d, g, stream));
 }
 
 kata_status_t prefill(const void* k, const void* v, float* S, float* z, int B, int H, int T,
@@ -517,7 +537,7 @@ kata_status_t kata_fwd_quadratic(const void* q, const void* k, const void* v, fl
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out)) return KATA_ERR_INVALID_ARG;
   const kata_status_t c = quad_check(B, H, T, d, dv, dtype, 1);
   if (c != KATA_OK) return c;
-  const size_t bytes = kata::mfma_quadratic_workspace(B * H, T, dv);
+  const size_t bytes = quad_workspace(B * H, T, dv);
   void* ws = nullptr;
   if (alloc_ws(&ws, bytes, stream) != KATA_OK) return KATA_ERR_HIP;
   const kata_status_t st = quad_ws(q, k, v, out, B, H, T, d, dv, 1, dtype, ws, bytes, stream);

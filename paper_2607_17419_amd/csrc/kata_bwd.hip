@@ -1026,3 +1026,5 @@ template hipError_t launch_bwd<bf16_t>(const void*, const void*, const void*, co
                                        int, int, int, int, int, void*, hipStream_t, hipEvent_t*);
 
 }  // namespace kata
+
+#include "kata_bwd_quad.hpp"

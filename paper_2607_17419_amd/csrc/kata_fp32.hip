@@ -616,3 +616,5 @@ template hipError_t launch_decode<bf16_t>(float*, float*, const void*, const voi
                                           float*, int, int, int, int, hipStream_t);
 
 }  // namespace kata
+
+#include "kata_quad32.hpp"

@@ -37,7 +37,7 @@ template <typename Tin>
 hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const void* v,
                          float* out, int BH, int d, int dv, int g, hipStream_t st);
 
-// ---- quadratic form in fp32 (kata_quad32.hip) -------------------------------
+// ---- quadratic form in fp32 (kata_quad32.hpp) -------------------------------
 // g = 1; d <= 64, dv <= 256 (gradients: dv <= 64).  The gradients use dv + 1
 // floats of workspace per token and two per head; ev as for launch_bwd.
 bool quad32_fwd_ok(int BH, int T, int d, int g);
@@ -59,9 +59,12 @@ size_t mfma_forward_workspace(int BH, int T, int d, int dv, int L, int g);
 hipError_t launch_mfma_forward(const void* q, const void* k, const void* v, float* out, float* den,
                                int BH, int T, int d, int dv, int g, int L, void* ws,
                                hipStream_t st, hipEvent_t* ev);
-size_t mfma_quadratic_workspace(int BH, int T, int dv);
-hipError_t launch_mfma_quadratic(const void* q, const void* k, const void* v, float* out, int BH,
-                                 int T, int d, int dv, int g, void* ws, hipStream_t st);
+// ---- quadratic form in bf16 (kata_quad_fwd.hpp) ---------------------------------
+// The shapes of mfma_supported; den nullable.  quad_fwd_ok: whether it is the
+// faster form for a forward whose span is left to the library.
+bool quad_fwd_ok(int BH, int T, int d, int g);
+hipError_t launch_quad_fwd(const void* q, const void* k, const void* v, float* out, float* den,
+                           int BH, int T, int d, int g, hipStream_t st);
 
 // ---- linear features (kata_linear.hip) ------------------------------------
 // feature codes of kata_lin_feature_t
@@ -111,7 +114,7 @@ hipError_t launch_bwd_prefix_bf(bool backward, const void* x, const void* y, voi
 hipError_t launch_bwd_grad_bf(const void* q, const void* k, const void* v, const float* ab,
                               const void* frec, const void* brec, float* dq, float* dk,
                               float* dv_out, int BH, int T, hipStream_t st);
-// Gradients in the quadratic (flash-style) form (kata_bwd_quad.hip), for the
+// Gradients in the quadratic (flash-style) form (kata_bwd_quad.hpp), for the
 // shapes of bwd_bf_ok(); forms no records and uses 264 bytes of workspace per
 // token.  ev as for launch_bwd (the record intervals are empty).
 bool bwd_quad_ok(int BH, int T);

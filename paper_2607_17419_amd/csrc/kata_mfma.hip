@@ -48,17 +48,6 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Two state features k_x(t) k_y(t), k_x(t+1) k_y(t+1) from a bf16 pair of y
-// values and the matching packed pair of x values, rounded to one bf16 pair.
-// Each v_dot2 has one zero lane, so it returns the exact product.
-__device__ __forceinline__ uint32_t gen_pair(bf16x2 y2, uint32_t xw) {
-  const float p0 = __builtin_amdgcn_fdot2_f32_bf16(y2, __builtin_bit_cast(bf16x2, xw & 0x0000FFFFu),
-                                                   0.f, false);
-  const float p1 = __builtin_amdgcn_fdot2_f32_bf16(y2, __builtin_bit_cast(bf16x2, xw & 0xFFFF0000u),
-                                                   0.f, false);
-  return pack_bf16x2(p0, p1);
-}
-
 __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -179,21 +168,6 @@ __device__ __forceinline__ void g2lds16(const void* gsrc, void* lds_wave_base) {
 __device__ __forceinline__ uint32_t word_of(const bf16x8& f, int j) {
   const uint4 w = __builtin_bit_cast(uint4, f);
   return j == 0 ? w.x : (j == 1 ? w.y : (j == 2 ? w.z : w.w));
-}
-
-// Single MFMAs for sequences whose order the caller fixes with scheduling
-// barriers (compiler builtins: the compiler inserts the wait states between
-// an MFMA and the VALU instructions around it): mfma_a and mfma_v accumulate,
-// mfma_vz starts a chain from zero.
-__device__ __forceinline__ void mfma_a(f32x16& acc, const bf16x8& a, const bf16x8& b) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-}
-__device__ __forceinline__ void mfma_vz(f32x16& acc, const bf16x8& a, const bf16x8& b) {
-  const f32x16 z = {};
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, z, 0, 0, 0);
-}
-__device__ __forceinline__ void mfma_v(f32x16& acc, const bf16x8& a, const bf16x8& b) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
 }
 
 // Keeps the operand registers of recently issued MFMAs live up to this point,
@@ -758,20 +732,11 @@ __global__ __launch_bounds__((64 * StateGrid<D, DV, NG>::NW)) void span_state_ke
 }
 
 // ---------------------------------------------------------------------------
-// Quadratic form (and the stage buffers of K4).  quadratic_kernel: 1-D grid
-// of workgroups of 256 threads (4 waves), one per CU (LDS: the five 32 KB
-// stage buffers, of which it uses three).  A head (one span covering the
-// sequence) has QB = T/256 query blocks; block id -> (head, query block)
-// keeps the query blocks of a head on one XCD (equal id % 8) so they share
-// its keys in that XCD's L2.  The workgroup owns 8 query tiles of 32; wave w
-// takes tiles {w, 7-w}, which balances the causal work.  Operands are staged
-// by direct global -> LDS copies, three stages deep, so no registers hold
-// staged data and the copies of stage s+2 overlap the arithmetic of stage s.
-// LDS fragment reads use per-lane offsets computed once, so every read is a
-// base register plus an immediate.
-// pre[bh][s][E] bf16 (K4): weighted S_pre^T as [dv][NSLOT], then Z_pre
-// (operand order).  K4 stages K and V rows as they are in HBM; the quadratic
-// form reads vtp[bh][dv][LA] bf16, a permuted V^T (vt_permute_kernel).
+// The stage buffers of K4 (K3's weighted prefix records pre[bh][s][E] bf16:
+// S_pre^T as [dv][NSLOT], then Z_pre in operand order): operands are staged by
+// direct global -> LDS copies several stages deep, so no registers hold staged
+// data.  LDS fragment reads use per-lane offsets computed once, so every read is
+// a base register plus an immediate.
 // ---------------------------------------------------------------------------
 constexpr int kKB = 128;        // keys per intra stage (four 32-key blocks)
 constexpr int kKC = 16;         // readout K-steps per stage
@@ -802,454 +767,10 @@ __device__ __forceinline__ uint2 lds_tr16(const void* p) {
 }
 
 
-// Scores of two query tiles against one 32-key block: sc_i = K_blk Q_i^T
-// over the d-contraction, the two accumulation chains interleaved (compiler
-// builtins; the compiler inserts the wait states before the VALU reads them).
-template <int KZ>
-__device__ __forceinline__ void score2(f32x16& sc0, f32x16& sc1, const bf16x8 (&A)[KZ],
-                                       const bf16x8 (&q0)[KZ], const bf16x8 (&q1)[KZ]) {
-  mfma_vz(sc0, A[0], q0[0]);
-  mfma_vz(sc1, A[0], q1[0]);
-#pragma unroll
-  for (int kz = 1; kz < KZ; ++kz) {
-    mfma_v(sc0, A[kz], q0[kz]);
-    mfma_v(sc1, A[kz], q1[kz]);
-  }
-}
-
-// Scores of two query tiles against one 32-key block with two feature blocks
-// of 32 coordinates (K-steps 0, 1 of block 0 and 2, 3 of block 1): four
-// chains, interleaved.
-__device__ __forceinline__ void score2b2(f32x16& s00, f32x16& s01, f32x16& s10, f32x16& s11,
-                                         const bf16x8 (&A)[4], const bf16x8 (&q0)[4],
-                                         const bf16x8 (&q1)[4]) {
-  mfma_vz(s00, A[0], q0[0]);
-  mfma_vz(s10, A[0], q1[0]);
-  mfma_vz(s01, A[2], q0[2]);
-  mfma_vz(s11, A[2], q1[2]);
-  mfma_v(s00, A[1], q0[1]);
-  mfma_v(s10, A[1], q1[1]);
-  mfma_v(s01, A[3], q0[3]);
-  mfma_v(s11, A[3], q1[3]);
-}
-
-template <int D, int DV>
-struct OutGrid {
-  static constexpr int QB_TOKENS = 256;  // queries per workgroup
-};
-
-template <int D, int DV, int NG>
-__global__ __launch_bounds__(256) void quadratic_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-    const uint16_t* __restrict__ vtp, float* __restrict__ out, int T, int L, int LV, int NS,
-    int QB, int sp0, int nsp) {
-  using G = GeoG<D, DV, NG>;
-  constexpr int DM = G::DM, RM = G::RM, KZM = G::KZM;
-  constexpr int NQ = 2, W = 4, NT = 8;
-  constexpr int KCH = D / 8;                    // 16-byte chunks per key row
-  constexpr int KCHUNKS = kKB * KCH;            // K rows of one intra stage
-  constexpr int VCH = kKB / 8;                  // chunks per V^T row of one stage (16)
-  constexpr int VCHUNKS = DV * VCH;
-  constexpr int ICH = KCHUNKS + VCHUNKS;        // chunks per intra stage
-  static_assert(ICH * 16 <= kStageBytes && KCHUNKS % 256 == 0 && VCHUNKS % 256 == 0,
-                "intra stage size");
-  constexpr int IPW_K = KCHUNKS / 256;          // copy instructions per wave: K rows
-  constexpr int IPW_I = ICH / 256;              // ... K rows then V^T rows
-  static_assert(G::MT == 2, "two dv tiles");
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane & 31, g = lane >> 5;
-  const int id = blockIdx.x;
-  const int jx = id >> 3;
-  // query blocks differ in work by up to a factor QB: the longest go first
-  const int qb = QB - 1 - jx % QB;
-  const int sp = sp0 + 8 * (jx / QB) + (id & 7);
-  if (sp >= nsp) return;  // whole workgroup: padding of the grid
-  const int s = sp % NS, bh = sp / NS;
-  const long long span0 = static_cast<long long>(s) * L;
-  const long long span_end = min(static_cast<long long>(T), span0 + L);
-  const long long wg_q0 = span0 + static_cast<long long>(qb) * NT * 32;
-  if (wg_q0 >= span_end) return;  // whole workgroup beyond the sequence
-  const uint16_t* qh = q + static_cast<long long>(bh) * T * D;
-  const uint16_t* kh = k + static_cast<long long>(bh) * T * D;
-  const uint16_t* vt_rec = vtp + static_cast<long long>(sp) * DV * LV;
-
-  int tile[NQ];
-  long long tq0[NQ];
-  bool tlive[NQ];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const int local = (i == 0) ? wave : 2 * W - 1 - wave;
-    tile[i] = qb * NT + local;
-    tq0[i] = span0 + 32LL * tile[i];
-    tlive[i] = tq0[i] < span_end;
-  }
-
-  // ---- staging copies of both phases ------------------------------------------
-  // Stages cover the key blocks of the workgroup's last live tile; every
-  // wave runs all of them (the stage barriers are workgroup-wide).
-  int last_tile = qb * NT + NT - 1;
-  const int last_key_tile = static_cast<int>((span_end - 1 - span0) / 32);
-  if (last_tile > last_key_tile) last_tile = last_key_tile;
-  const int nstage = (last_tile + 1 + 3) / 4;  // 128-key intra stages
-  // intra copy i of this lane: K row / V^T row and the chunk it fetches
-  int ksrc[IPW_K];  // element offset of the K chunk from the stage's first key row
-  int vsrc[IPW_I - IPW_K];
-#pragma unroll
-  for (int i = 0; i < IPW_I; ++i) {
-    const int P = (i * W + wave) * 64 + lane;  // LDS chunk written by this lane
-    if (i < IPW_K) {
-      const int r = P / KCH, pos = P % KCH;
-      ksrc[i] = r * D + 8 * (pos ^ kswz<D>(r));
-    } else {
-      const int P2 = P - KCHUNKS;
-      const int m = P2 / VCH, pos = P2 % VCH;
-      vsrc[i - IPW_K] = m * LV + 8 * (pos ^ rswz(m));
-    }
-  }
-  auto issue_i = [&](int st, uint16_t* buf) __attribute__((always_inline)) {
-    const long long key0 = span0 + static_cast<long long>(st) * kKB;
-#pragma unroll
-    for (int i = 0; i < IPW_I; ++i) {
-      const void* src;
-      if (i < IPW_K) {
-        // keys past the sequence: re-read the last row (never used)
-        const long long over = key0 + ksrc[i] / D - (T - 1);
-        src = kh + key0 * D + ksrc[i] - (over > 0 ? over * D : 0);
-      } else {
-        src = vt_rec + st * kKB + vsrc[i - IPW_K];
-      }
-      g2lds16(src, buf + (i * W + wave) * 512);
-    }
-  };
-  // Stage 0 is issued first and the query fragments are loaded behind it;
-  // the workgroup waits for that one memory round trip (the compiler's wait
-  // before the empty asm below: loads complete in order, so it also covers
-  // the copies issued before them), and only then issues stage 1, which
-  // arrives under the first stage's work.  From here on the only vector
-  // memory operations in flight are copies (and the final stores), which the
-  // pipeline's own waits count.
-  issue_i(0, g_stage0);
-
-  // bf16 query fragments for the d-contractions, per feature block:
-  // qf[i][KZM*bb + kz] holds q[t][DM*bb + 8*kz + RM*g .. +7] of this lane's
-  // query t = tq0 + c (with one block: q[t][8*kz + R*g ..]).
-  bf16x8 qf[NQ][G::KZ];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const long long t = min(tq0[i] + c, static_cast<long long>(T) - 1);
-#pragma unroll
-    for (int kz = 0; kz < G::KZ; ++kz)
-      qf[i][kz] = *reinterpret_cast<const bf16x8*>(qh + t * D + DM * (kz / KZM) +
-                                                   8 * (kz % KZM) + RM * g);
-  }
-
-#pragma unroll
-  for (int i = 0; i < NQ; ++i)
-#pragma unroll
-    for (int kz = 0; kz < G::KZ; ++kz) asm volatile("" ::"v"(qf[i][kz]));
-  if (nstage > 1) issue_i(1, g_stage1);
-
-  // the P V accumulators
-  f32x16 acc[G::MT][NQ];
-#pragma unroll
-  for (int m = 0; m < G::MT; ++m)
-#pragma unroll
-    for (int i = 0; i < NQ; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[m][i][r] = 0.f;
-  float dpart[NQ];  // the denominators' row sums
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) dpart[i] = 0.f;
-
-  // ---- causal squared-score attention inside the span -----------------------
-  // Per 32-key block kb and query tile i: S_i = K_kb Q_i^T (a chain of KZ
-  // MFMAs into VGPRs), P_i = S_i^2 masked above the diagonal on the tile's
-  // diagonal block (VALU, with the row sums for the denominator), and
-  // O_i += V_kb^T P_i (four MFMAs: two dv halves x two 16-key halves).  The
-  // wave's two tiles run half a block apart, so every VALU step has MFMAs of
-  // the other tile to issue between:
-  //   group A of block kb: S_0(kb) and P V of tile 0 at kb-1; P_1(kb-1)
-  //   group B of block kb: S_1(kb) and P V of tile 1 at kb-1; P_0(kb)
-  // A wave issues in order and an MFMA holds the matrix pipe for 32 cycles;
-  // each group alternates its two MFMA chains (never two dependent MFMAs in a
-  // row) and places a quarter of the P work after each MFMA (scheduling
-  // barriers keep that order).  A tile whose diagonal block is past, or that
-  // lies beyond the sequence, gets zero P fragments: its MFMAs still run, so
-  // no branch surrounds an accumulator.
-  {
-    // fragment byte offsets inside a stage buffer
-    //  K rows 32*sb + c, chunk (DM/8)*bb + kz' + (RM/8)*g of fragment KZM*bb + kz'
-    //  (the layout of qf), ^ kswz: depends on sb only through sb & 1
-    unsigned kfo[2][G::KZ];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int kz = 0; kz < G::KZ; ++kz) {
-        const int krow = 32 * h + c;
-        const int chunk = (DM / 8) * (kz / KZM) + (kz % KZM) + (RM / 8) * g;
-        kfo[h][kz] = static_cast<unsigned>((krow * KCH + (chunk ^ kswz<D>(krow))) * 16);
-      }
-    //  V^T rows 32*m + c, chunk (4*sb + 2*kv + g) ^ (c & 15); the row part of m is immediate
-    unsigned vfo[4][2];
-#pragma unroll
-    for (int sb = 0; sb < 4; ++sb)
-#pragma unroll
-      for (int kv = 0; kv < 2; ++kv)
-        vfo[sb][kv] = static_cast<unsigned>(
-            (KCHUNKS + c * VCH + ((4 * sb + 2 * kv + g) ^ rswz(c))) * 16);
-
-    // a tile's diagonal block, -1 for a tile beyond the sequence (wave-uniform)
-    int tdiag[NQ];
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) tdiag[i] = __builtin_amdgcn_readfirstlane(tlive[i] ? tile[i] : -1);
-    // Fragment loads of block kb at stage position sb (known at compile time)
-    // from its stage buffer; one 16-byte read per call, so that the callers
-    // can spread them over the MFMA slots of a group.
-    auto ldA1 = [&](const char* buf, auto sb_c, int kz, bf16x8& dst) __attribute__((always_inline)) {
-      constexpr int sb = decltype(sb_c)::value;
-      dst = *reinterpret_cast<const bf16x8*>(buf + (sb >> 1) * (64 * KCH * 16) + kfo[sb & 1][kz]);
-    };
-    auto ldV1 = [&](const char* buf, auto sb_c, int m, int kv, bf16x8& dst)
-                    __attribute__((always_inline)) {
-      constexpr int sb = decltype(sb_c)::value;
-      dst = *reinterpret_cast<const bf16x8*>(buf + vfo[sb][kv] + m * (32 * VCH * 16));
-    };
-    auto ldA = [&](const char* buf, auto sb_c, bf16x8 (&A)[G::KZ]) __attribute__((always_inline)) {
-#pragma unroll
-      for (int kz = 0; kz < G::KZ; ++kz) ldA1(buf, sb_c, kz, A[kz]);
-    };
-    auto ldV = [&](const char* buf, auto sb_c, bf16x8 (&va)[G::MT][2]) __attribute__((always_inline)) {
-#pragma unroll
-      for (int m = 0; m < G::MT; ++m)
-#pragma unroll
-        for (int kv = 0; kv < 2; ++kv) ldV1(buf, sb_c, m, kv, va[m][kv]);
-    };
-    // Score accumulators of one query tile: one per feature block; the weight
-    // of a (query, key) pair is the sum over blocks of the squared scores.
-    struct Sc {
-      f32x16 b[NG];
-    };
-    auto p_of = [](const Sc& sc, int r) __attribute__((always_inline)) {
-      float p = sc.b[0][r] * sc.b[0][r];
-#pragma unroll
-      for (int bb = 1; bb < NG; ++bb) p += sc.b[bb][r] * sc.b[bb][r];
-      return p;
-    };
-    // P elements 2j and 2j+1 of a tile on a block before its diagonal, packed.
-    // The empty asm statement consumes the results before the next asm (an
-    // MFMA), so the compiler can neither sink the part below it nor merge it
-    // into the fix-up that follows the group.
-    auto ppart = [&](int j, const Sc& sc, float& dacc, uint32_t (&bw)[8])
-                     __attribute__((always_inline)) {
-      const float p0 = p_of(sc, 2 * j);
-      const float p1 = p_of(sc, 2 * j + 1);
-      dacc += p0 + p1;
-      bw[j] = pack_bf16x2(p0, p1);
-      asm volatile("" : "+v"(dacc), "+v"(bw[j]));
-    };
-    // on tile i's diagonal block (keys above the query masked) and past it
-    // (zero; also a tile beyond the sequence) the tile's P of block kb is
-    // redone after its group, VALU only; dsave is the row sum before the group
-    auto fixup = [&](int kb, int i, const Sc& sc, float dsave, float& dacc, uint32_t (&bw)[8])
-                     __attribute__((always_inline)) {
-      if (__builtin_expect(kb < tdiag[i], 1)) return;  // nothing to redo (the common case)
-      if (kb == tdiag[i]) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int r0 = 2 * j, r1 = 2 * j + 1;
-          const float p0 = (8 * (r0 >> 2) + 4 * g + (r0 & 3) > c) ? 0.f : p_of(sc, r0);
-          const float p1 = (8 * (r1 >> 2) + 4 * g + (r1 & 3) > c) ? 0.f : p_of(sc, r1);
-          dsave += p0 + p1;
-          bw[j] = pack_bf16x2(p0, p1);
-        }
-        dacc = dsave;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) bw[j] = 0u;
-        dacc = dsave;
-      }
-    };
-    auto bfrag = [](const uint32_t (&bw)[8], int kv) __attribute__((always_inline)) {
-      return __builtin_bit_cast(bf16x8, make_uint4(bw[4 * kv], bw[4 * kv + 1], bw[4 * kv + 2],
-                                                   bw[4 * kv + 3]));
-    };
-    // one group: score chains into scs (if S), P V into (a0, a1) from fragments
-    // vb and P words bv (if V), and the P words bw of the other tile from scp
-    // (full mode; the caller fixes them up for the other modes); extra(i)
-    // adds the caller's work (fragment loads) to slot i.  Score MFMA i is
-    // K-step i / NG of block i % NG, so consecutive MFMAs of one chain are NG
-    // slots apart.
-    auto group = [&](auto s_c, auto v_c, Sc& scs, const bf16x8 (&Ab)[G::KZ],
-                     const bf16x8 (&qs)[G::KZ], f32x16& a0, f32x16& a1,
-                     const bf16x8 (&vb)[G::MT][2], const uint32_t (&bv)[8], Sc& scp,
-                     float& dacc, uint32_t (&bw)[8], auto&& extra) __attribute__((always_inline)) {
-      constexpr bool HS = decltype(s_c)::value, HV = decltype(v_c)::value;
-      bf16x8 Bv[2];
-      if constexpr (HV) {
-        Bv[0] = bfrag(bv, 0);
-        Bv[1] = bfrag(bv, 1);
-      }
-      static_for<0, 4>([&](auto i_c) {
-        constexpr int i = decltype(i_c)::value;
-        if constexpr (HS && i < G::KZ) {
-          constexpr int bb = i % NG, kz = KZM * bb + i / NG;
-          if constexpr (i / NG == 0) mfma_vz(scs.b[bb], Ab[kz], qs[kz]);
-          else mfma_v(scs.b[bb], Ab[kz], qs[kz]);
-        }
-        // without a score chain the P V MFMA goes first, so that the VALU
-        // reads scp two MFMA issues after the chain that wrote it
-        if constexpr (!HS && HV) mfma_a((i & 1) ? a1 : a0, vb[i & 1][i >> 1], Bv[i >> 1]);
-        // the scores become available to the VALU only after the first MFMA
-        if constexpr (i == 0) {
-#pragma unroll
-          for (int bb = 0; bb < NG; ++bb) asm volatile("" : "+v"(scp.b[bb]));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        ppart(2 * i, scp, dacc, bw);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (HS && HV) mfma_a((i & 1) ? a1 : a0, vb[i & 1][i >> 1], Bv[i >> 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        ppart(2 * i + 1, scp, dacc, bw);
-        extra(i_c);
-        __builtin_amdgcn_sched_barrier(0);
-      });
-    };
-    auto none = [](auto) {};
-    using Yes = std::true_type;
-    using No = std::false_type;
-    using std::integral_constant;
-
-    const int NB = 4 * nstage;  // 32-key blocks, all waves alike (stage barriers)
-    bf16x8 A[2][G::KZ], va[2][G::MT][2];
-    Sc sc[NQ];
-    uint32_t bw[NQ][8];
-    // stage buffers of stages st, st+1, st+2 (rotated once per stage)
-    const char* b0 = reinterpret_cast<const char*>(g_stage0);
-    const char* b1 = reinterpret_cast<const char*>(g_stage1);
-    const char* b2 = reinterpret_cast<const char*>(g_stage2);
-    // stage 0 (its copies were waited for with the query fragments)
-    lds_barrier();
-    if (nstage > 2) issue_i(2, g_stage2);
-    ldA(b0, integral_constant<int, 0>{}, A[0]);
-    ldA(b0, integral_constant<int, 1>{}, A[1]);
-    ldV(b0, integral_constant<int, 0>{}, va[0]);
-    // block 0: both score chains interleaved (no earlier block to finish),
-    // then P_0(0); score2 leaves sc[0] readable by VALU
-    if constexpr (NG == 1) score2<G::KZ>(sc[0].b[0], sc[1].b[0], A[0], qf[0], qf[1]);
-    else score2b2(sc[0].b[0], sc[0].b[1], sc[1].b[0], sc[1].b[1], A[0], qf[0], qf[1]);
-    {
-      const float dsave = dpart[0];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) ppart(j, sc[0], dpart[0], bw[0]);
-      fixup(0, 0, sc[0], dsave, dpart[0], bw[0]);
-    }
-    // block kb >= 1 at stage position sb: A[sb & 1] holds A(kb) and V(kb) is
-    // loaded into va[sb & 1]; P V of block kb-1 uses va[(sb & 1) ^ 1].  Inside
-    // a stage the loads of V(kb) and A(kb+1) ride in group A's MFMA slots; the
-    // last block of a stage loads up front, around the stage change.
-    auto step = [&](auto sb_c, int kb) __attribute__((always_inline)) {
-      constexpr int sb = decltype(sb_c)::value;
-      constexpr int cur = sb & 1;
-      auto loads = [&](auto i_c) __attribute__((always_inline)) {
-        constexpr int i = decltype(i_c)::value;
-        if constexpr (sb != 3) {
-          if constexpr (i < 2) {
-            ldV1(b0, sb_c, i, 0, va[cur][i][0]);
-            ldV1(b0, sb_c, i, 1, va[cur][i][1]);
-          } else {
-#pragma unroll
-            for (int kz = 2 * (i - 2); kz < 2 * (i - 2) + 2; ++kz)
-              if (kz < G::KZ) ldA1(b0, integral_constant<int, sb + 1>{}, kz, A[cur ^ 1][kz]);
-          }
-        }
-      };
-      if constexpr (sb == 3) {
-        ldV(b0, sb_c, va[cur]);
-        if (kb + 1 < NB) {  // block kb+1 opens stage st
-          const int st = (kb + 1) >> 2;
-          if (st + 1 < nstage) wait_vmcnt<IPW_I>(); else wait_vmcnt<0>();
-          lds_barrier();  // also: every wave has read stage st-1 (V(kb) above)
-          if (st + 2 < nstage) issue_i(st + 2, const_cast<uint16_t*>(reinterpret_cast<const uint16_t*>(b0)));
-          ldA(b1, integral_constant<int, 0>{}, A[cur ^ 1]);
-        }
-      }
-      {
-        const float dsave = dpart[1];
-        group(Yes{}, Yes{}, sc[0], A[cur], qf[0], acc[0][0], acc[1][0], va[cur ^ 1], bw[0], sc[1],
-              dpart[1], bw[1], loads);
-        fixup(kb - 1, 1, sc[1], dsave, dpart[1], bw[1]);
-      }
-      {
-        const float dsave = dpart[0];
-        group(Yes{}, Yes{}, sc[1], A[cur], qf[1], acc[0][1], acc[1][1], va[cur ^ 1], bw[1], sc[0],
-              dpart[0], bw[0], none);
-        fixup(kb, 0, sc[0], dsave, dpart[0], bw[0]);
-      }
-    };
-    auto rotate = [&]() __attribute__((always_inline)) {
-      const char* t = b0;
-      b0 = b1;
-      b1 = b2;
-      b2 = t;
-    };
-    step(integral_constant<int, 1>{}, 1);
-    step(integral_constant<int, 2>{}, 2);
-    step(integral_constant<int, 3>{}, 3);
-    rotate();
-    for (int st = 1; st < nstage; ++st) {
-      step(integral_constant<int, 0>{}, 4 * st);
-      step(integral_constant<int, 1>{}, 4 * st + 1);
-      step(integral_constant<int, 2>{}, 4 * st + 2);
-      step(integral_constant<int, 3>{}, 4 * st + 3);
-      rotate();
-    }
-    // finish the last block (kb = NB - 1, odd): P V of both tiles
-    {
-      const float dsave = dpart[1];
-      group(No{}, Yes{}, sc[0], A[0], qf[0], acc[0][0], acc[1][0], va[1], bw[0], sc[1], dpart[1],
-            bw[1], none);
-      fixup(NB - 1, 1, sc[1], dsave, dpart[1], bw[1]);
-    }
-    {
-      // no P left to compute: the VALU parts of this group redo P_0 of the
-      // last block into a scratch copy, which is discarded
-      float dd = 0.f;
-      uint32_t bx[8];
-      group(No{}, Yes{}, sc[1], A[0], qf[1], acc[0][1], acc[1][1], va[1], bw[1], sc[0], dd, bx,
-            none);
-      hold(bx[0]);
-    }
-  }
-
-  // ---- normalise and store ---------------------------------------------------
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const float Dt = dpart[i] + __shfl_xor(dpart[i], 32);
-    const long long t = tq0[i] + c;
-    if (!tlive[i] || t >= span_end) continue;
-    const float inv = (Dt > 0.f) ? 1.f / Dt : 0.f;
-    float* orow = out + (static_cast<long long>(bh) * T + t) * DV;
-#pragma unroll
-    for (int m = 0; m < G::MT; ++m)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        float4 o;
-        o.x = acc[m][i][4 * r4 + 0] * inv;
-        o.y = acc[m][i][4 * r4 + 1] * inv;
-        o.z = acc[m][i][4 * r4 + 2] * inv;
-        o.w = acc[m][i][4 * r4 + 3] * inv;
-        *reinterpret_cast<float4*>(orow + 32 * m + 8 * r4 + 4 * g) = o;
-      }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // K4: span output, eight-wave form (dv = 64; d = 64 with one or two feature
-// blocks, d = 32).  The in-span loop and stage buffers of quadratic_kernel
-// with the prefix readout added, and 512 threads owning 512
+// blocks, d = 32): causal squared-score attention inside the span, the prefix
+// readout and the normalisation, 512 threads owning 512
 // queries (16 tiles of 32): wave w holds tiles w and 15 - w, so two waves
 // share each SIMD with balanced causal work (waves w and w + 4 hold tiles
 // adding up to 30), and one wave's VALU work (squared scores, query feature
@@ -1715,52 +1236,6 @@ __global__ __launch_bounds__(512) void span_output8_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// V^T of the keys key_base .. key_base + LV - 1 of every head, into
-// vtp + bh out_bh + out0 as [dv][LV] bf16, keys of every 16-key group in the
-// order 0-3, 8-11, 4-7, 12-15 (the key order of the quadratic kernel's P V
-// product), keys at or past T zero: the whole head for the quadratic form.
-// A workgroup transposes 64 keys through LDS.
-// grid (LV / 64, BH), block 256.
-// ---------------------------------------------------------------------------
-template <int DV>
-__global__ __launch_bounds__(256) void vt_permute_kernel(const uint16_t* __restrict__ v,
-                                                         uint16_t* __restrict__ vtp, int T,
-                                                         int LV, int key_base,
-                                                         long long out_bh, long long out0) {
-  constexpr int KEYS = 64, CH = DV / 8;  // keys per workgroup, 16-byte chunks per V row
-  __shared__ uint32_t tile[KEYS][DV / 2 + 1];  // [key][dv pair], one word of padding
-  const int bh = blockIdx.y;
-  const long long key0 = static_cast<long long>(blockIdx.x) * KEYS;
-  const uint16_t* vh = v + (static_cast<long long>(bh) * T + key_base) * DV;
-  const long long nkeys = static_cast<long long>(T) - key_base;
-  for (int i = threadIdx.x; i < KEYS * CH; i += 256) {
-    const int key = i / CH, ch = i % CH;
-    uint4 x = make_uint4(0u, 0u, 0u, 0u);
-    if (key0 + key < nkeys) x = *reinterpret_cast<const uint4*>(vh + (key0 + key) * DV + 8 * ch);
-    tile[key][4 * ch + 0] = x.x;
-    tile[key][4 * ch + 1] = x.y;
-    tile[key][4 * ch + 2] = x.z;
-    tile[key][4 * ch + 3] = x.w;
-  }
-  __syncthreads();
-  uint16_t* out = vtp + bh * out_bh + out0;
-  for (int i = threadIdx.x; i < DV * (KEYS / 8); i += 256) {
-    const int m = i / (KEYS / 8), h = i % (KEYS / 8);  // dv row, output chunk of 8 keys
-    const int base = 16 * (h >> 1) + 4 * (h & 1);        // keys base+0..3, base+8..11
-    uint16_t e[8];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t w0 = tile[base + j][m >> 1], w1 = tile[base + 8 + j][m >> 1];
-      e[j] = static_cast<uint16_t>((m & 1) ? (w0 >> 16) : w0);
-      e[4 + j] = static_cast<uint16_t>((m & 1) ? (w1 >> 16) : w1);
-    }
-    *reinterpret_cast<uint4*>(out + static_cast<long long>(m) * LV + key0 + 8 * h) =
-        make_uint4(e[0] | (static_cast<uint32_t>(e[1]) << 16), e[2] | (static_cast<uint32_t>(e[3]) << 16),
-                   e[4] | (static_cast<uint32_t>(e[5]) << 16), e[6] | (static_cast<uint32_t>(e[7]) << 16));
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
 bool mfma_supported(int d, int dv, int C, int g) {
@@ -1774,10 +1249,6 @@ static long long mfma_record(int d, int g) {
 }
 
 static size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
-
-// Sequence length rounded up to whole intra stages so that every staged key
-// block of the quadratic form lies inside its V^T copy.
-static int span_alloc(int L) { return (L + kKB - 1) / kKB * kKB; }
 
 constexpr int kSpansPerLaunch = 1 << 20;
 
@@ -1826,43 +1297,6 @@ static hipError_t run_mfma(const void* q, const void* k, const void* v, float* o
   return record(ev, 3, st);
 }
 
-// Quadratic form: one span per head covering the whole sequence, no state,
-// no scan, no prefix readout; the workspace holds the permuted V^T.
-size_t mfma_quadratic_workspace(int BH, int T, int dv) {
-  return align256(static_cast<size_t>(BH) * dv * span_alloc(T) * sizeof(uint16_t));
-}
-
-template <int D, int DV, int NG>
-static hipError_t run_quadratic(const void* q, const void* k, const void* v, float* out, int BH,
-                                int T, void* ws, hipStream_t st) {
-  const int LA = span_alloc(T);
-  static_assert(kKB % 64 == 0, "the transpose writes whole 64-key groups");
-  uint16_t* vtp = static_cast<uint16_t*>(ws);
-  vt_permute_kernel<DV><<<dim3(static_cast<unsigned>(LA / 64), static_cast<unsigned>(BH)), 256, 0,
-                          st>>>(static_cast<const uint16_t*>(v), vtp, T, LA, 0,
-                                static_cast<long long>(DV) * LA, 0LL);
-  const int qblocks = (T + OutGrid<D, DV>::QB_TOKENS - 1) / OutGrid<D, DV>::QB_TOKENS;
-  // 8 * qblocks * ceil(cnt / 8) workgroups per launch, below 2^31
-  int per = static_cast<int>((0x7fffffffLL / (8LL * qblocks)) * 8);
-  if (per > kSpansPerLaunch) per = kSpansPerLaunch;
-  for (int sp0 = 0; sp0 < BH; sp0 += per) {
-    const int cnt = BH - sp0 < per ? BH - sp0 : per;
-    const unsigned nb4 = 8u * static_cast<unsigned>(qblocks) * static_cast<unsigned>((cnt + 7) / 8);
-    quadratic_kernel<D, DV, NG><<<nb4, 256, 0, st>>>(static_cast<const uint16_t*>(q),
-                                                     static_cast<const uint16_t*>(k), vtp, out, T,
-                                                     T, LA, 1, qblocks, sp0, sp0 + cnt);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_mfma_quadratic(const void* q, const void* k, const void* v, float* out, int BH,
-                                 int T, int d, int dv, int g, void* ws, hipStream_t st) {
-  if (d == 64 && dv == 64 && g == 1) return run_quadratic<64, 64, 1>(q, k, v, out, BH, T, ws, st);
-  if (d == 64 && dv == 64 && g == 2) return run_quadratic<64, 64, 2>(q, k, v, out, BH, T, ws, st);
-  if (d == 32 && dv == 64 && g == 1) return run_quadratic<32, 64, 1>(q, k, v, out, BH, T, ws, st);
-  return hipErrorInvalidValue;
-}
-
 hipError_t launch_mfma_forward(const void* q, const void* k, const void* v, float* out, float* den,
                                int BH, int T, int d, int dv, int g, int L, void* ws,
                                hipStream_t st, hipEvent_t* ev) {
@@ -1876,3 +1310,5 @@ hipError_t launch_mfma_forward(const void* q, const void* k, const void* v, floa
 }
 
 }  // namespace kata
+
+#include "kata_quad_fwd.hpp"

@@ -1,4 +1,4 @@
-// kata_quad32.hip -- KATA-M1 (one feature block) in the quadratic form with
+// kata_quad32.hpp -- KATA-M1 (one feature block) in the quadratic form with
 // fp32 arithmetic on the fp32 matrix cores (v_mfma_f32_32x32x2_f32): forward and
 // gradients for every shape of the fp32 paths with g = 1 (d <= 64; dv <= 256
 // forward, dv <= 64 gradients; fp32 or bf16 inputs).
@@ -31,6 +31,9 @@
 // i + DP/2, so a lane reads its half row in consecutive pieces, and result
 // register r is the B operand of a product over the result's rows, step r
 // taking rows row(r, 0) and row(r, 1).
+// (Kernels and launchers; part of kata_fp32.hip.)
+#pragma once
+
 #include <type_traits>
 
 #include "kata_common.hpp"
@@ -172,6 +175,7 @@ __device__ __forceinline__ float early_scores(const Tin* q, const Tin* k, int T,
   const Tin* qr = q + min(lane >> 3, T - 1) * d;
   const Tin* kr = k + min(lane & 7, T - 1) * d;
   double s = 0.0;
+  __builtin_assume(d > 0);
 #pragma unroll 8
   for (int x = 0; x < d; ++x)
     s = fma(static_cast<double>(to_f32(qr[x])), static_cast<double>(to_f32(kr[x])), s);
