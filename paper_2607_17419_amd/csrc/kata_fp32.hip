@@ -529,6 +529,125 @@ __global__ __launch_bounds__(256) void decode_step_f32(float* __restrict__ S,
 }
 
 // ---------------------------------------------------------------------------
+// The same step with 1024 threads per head, the first rows' and z's loads issued
+// before anything else, and k_a k_b and the weighted q_a q_b of every feature
+// formed once, in LDS, while they are on their way: with few heads, one
+// workgroup's latency is the step's (B1 H16 d64: 19.6 -> 13.3 us, near what one CU
+// reads and writes; splitting a head over workgroups by value columns needs a
+// second launch for z and took 17 us), and small heads (d = 32) are short enough
+// for the setup to show.  6, 11 and 17 rows in flight per thread: 14.0, 13.3, 13.5
+// us.  NT: state accesses past the caches, for states larger than they keep.
+// grid BH, block 1024; dv a power of two from 4 to 256.
+// ---------------------------------------------------------------------------
+constexpr int kWideThreads = 1024;
+constexpr int kWideUnroll = 11;  // rows per thread in flight
+constexpr int kWideZ = 3;        // z values per thread (n <= 2080)
+
+template <typename Tin, bool NT>
+__global__ __launch_bounds__(kWideThreads) void decode_wide_f32(
+    float* __restrict__ S, float* __restrict__ z, const Tin* __restrict__ q,
+    const Tin* __restrict__ k, const Tin* __restrict__ v, float* __restrict__ out, int d, int dv,
+    int g, unsigned inv_m) {
+  __shared__ float qs[64], ks[64];
+  __shared__ float2 pkq[2080];   // k_a k_b and w q_a q_b
+  __shared__ float red[16][260];  // per wave: the columns' sums, then den
+  const int m = d / g, nm = m * (m + 1) / 2, n = g * nm;
+  const long long bh = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int gq = dv / 4, rows = kWideThreads / gq;  // 16-byte pieces per row, rows per pass
+  const int r0 = tid / gq, col = 4 * (tid & (gq - 1));
+  float* Sh = S + bh * n * dv + col;
+  float* zh = z + bh * n;
+  float4 s[kWideUnroll];
+  auto fetch = [&](int f0) {
+#pragma unroll
+    for (int u = 0; u < kWideUnroll; ++u) {
+      const float* p = Sh + min(f0 + u * rows, n - 1) * dv;
+      s[u] = NT ? stream_load4(p) : *reinterpret_cast<const float4*>(p);
+    }
+  };
+  if (tid < d) {
+    qs[tid] = load_f32(q, bh * d + tid);
+    ks[tid] = load_f32(k, bh * d + tid);
+  }
+  float zv[kWideZ];
+#pragma unroll
+  for (int u = 0; u < kWideZ; ++u) zv[u] = zh[min(tid + kWideThreads * u, n - 1)];
+  float vv[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) vv[e] = load_f32(v, bh * dv + col + e);
+  fetch(r0);
+  __syncthreads();
+  for (int i = tid; i < d * m; i += kWideThreads) {
+    const int x = static_cast<int>((static_cast<unsigned>(i) * inv_m) >> 20);  // i / m
+    const int b = i - x * m, blk = static_cast<int>((static_cast<unsigned>(x) * inv_m) >> 20);
+    const int a = x - blk * m, y = blk * m + b;
+    if (b >= a)
+      pkq[blk * nm + packed_index(a, b, m)] =
+          make_float2(ks[x] * ks[y], ((a == b) ? 1.f : 2.f) * qs[x] * qs[y]);
+  }
+  __syncthreads();
+  float num[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int f0 = r0; f0 < n; f0 += kWideUnroll * rows) {
+    if (f0 != r0) fetch(f0);
+#pragma unroll
+    for (int u = 0; u < kWideUnroll; ++u) {
+      const int f = f0 + u * rows;
+      const bool in = f < n;
+      const float2 p = pkq[in ? f : n - 1];
+      s[u].x += p.x * vv[0];
+      s[u].y += p.x * vv[1];
+      s[u].z += p.x * vv[2];
+      s[u].w += p.x * vv[3];
+      if (in) {
+        if constexpr (NT) stream_store4(Sh + f * dv, s[u]);
+        else *reinterpret_cast<float4*>(Sh + f * dv) = s[u];
+      }
+      const float w = in ? p.y : 0.f;
+      num[0] += w * s[u].x;
+      num[1] += w * s[u].y;
+      num[2] += w * s[u].z;
+      num[3] += w * s[u].w;
+    }
+  }
+  float den = 0.f;
+#pragma unroll
+  for (int u = 0; u < kWideZ; ++u) {
+    const int f = tid + kWideThreads * u;
+    if (f < n) {
+      const float2 p = pkq[f];
+      const float zz = zv[u] + p.x;
+      zh[f] = zz;
+      den += p.y * zz;
+    }
+  }
+  // lanes of one column piece, then the waves
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    den += __shfl_xor(den, o);
+    if (o >= gq) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] += __shfl_xor(num[e], o);
+    }
+  }
+  if (lane < gq) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wv][col + e] = num[e];
+  }
+  if (lane == 0) red[wv][256] = den;
+  __syncthreads();
+  if (tid < dv) {
+    float D = 0.f, x = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      D += red[w][256];
+      x += red[w][tid];
+    }
+    out[bh * dv + tid] = (D > 0.f) ? x / D : 0.f;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
 size_t fp32_forward_workspace(int BH, int T, int d, int dv, int C, int g) {
@@ -594,6 +713,24 @@ hipError_t launch_prefill(const void* k, const void* v, float* S, float* z, int 
 template <typename Tin>
 hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const void* v,
                          float* out, int BH, int d, int dv, int g, hipStream_t st) {
+  // Measured (us, wide : 256 threads; d = 64, the same state each step / four in
+  // turn): 64 heads (34 MB) 16 / 18 : 29 / 29 cached; 128 heads 29 / 30 : 33 / 33
+  // and 256 heads (136 MB) 52 / 52 : 53 / 54 past the caches, 1024 heads 203 : 197;
+  // d = 32 (135 KB per head) 1024 heads 50 : 58, 4096 heads 186 : 207.
+  const int n = g * ((d / g) * (d / g + 1) / 2);
+  const size_t head = static_cast<size_t>(n) * dv * sizeof(float), state = head * BH;
+  const bool pow2 = dv >= 4 && dv <= 256 && (dv & (dv - 1)) == 0;
+  if (pow2 && (state <= (140u << 20) || head <= (160u << 10))) {
+    const unsigned m = d / g, inv_m = ((1u << 20) + m - 1) / m;  // exact quotients below 64 m
+    auto go = [&](auto nt) {
+      decode_wide_f32<Tin, decltype(nt)::value><<<BH, kWideThreads, 0, st>>>(
+          S, z, static_cast<const Tin*>(q), static_cast<const Tin*>(k), static_cast<const Tin*>(v),
+          out, d, dv, g, inv_m);
+    };
+    if (state <= (48u << 20)) go(std::false_type{});
+    else go(std::true_type{});
+    return hipGetLastError();
+  }
   decode_step_f32<Tin><<<BH, 256, 0, st>>>(S, z, static_cast<const Tin*>(q),
                                            static_cast<const Tin*>(k), static_cast<const Tin*>(v),
                                            out, d, dv, g);

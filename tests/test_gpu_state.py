@@ -79,3 +79,42 @@ def test_state_overflow_matches_fp32(kata):
     assert not torch.isnan(got).any() and torch.isinf(z.cpu()[0, 1]).sum() == 1
     fin = torch.isfinite(ref)
     assert torch.allclose(got[fin], ref[fin], rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("B,H,d,dv,g", [
+    (1, 1, 64, 64, 1), (1, 3, 1, 4, 1), (2, 2, 33, 32, 1), (1, 5, 24, 128, 3), (1, 2, 64, 256, 2),
+    (3, 1, 40, 8, 5), (1, 2, 48, 24, 1), (1, 2, 7, 5, 1), (6, 16, 64, 64, 1), (18, 16, 64, 64, 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_decode_step_forms(kata, dtype, B, H, d, dv, g):
+    """Few heads, many heads and value widths with and without a wide form: two
+    steps against fp64.  Each S, z entry takes one product and one addition, each
+    output sums n entries twice rounded; (n / 32 + 64) roundoffs of the magnitude
+    sums bound the order of any of the kernels' sums."""
+    import torch
+    log(f"case decode {dtype} B{B} H{H} d{d} dv{dv} g{g}")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    a, b = (torch.from_numpy(x).cuda() for x in _pairs(d, g))
+    n = a.numel()
+    S = torch.randn((B, H, n, dv), generator=gen, device="cuda")
+    z = torch.rand((B, H, n), generator=gen, device="cuda") + 4.0 * (a == b)
+    S64, z64 = S.double(), z.double()
+    for _ in range(2):
+        q, k = (torch.randn((B, H, d), generator=gen, device="cuda").to(tt) for _ in range(2))
+        v = torch.randn((B, H, dv), generator=gen, device="cuda").to(tt)
+        out = kata.mg_decode_step(S, z, q, k, v, g)
+        q6, k6, v6 = q.double(), k.double(), v.double()
+        pk = k6[..., a] * k6[..., b]
+        S64 += pk[..., None] * v6[:, :, None, :]
+        z64 += pk
+        assert float((S.double() - S64).abs().max()) <= 8 * U * float(S64.abs().max())
+        assert float((z.double() - z64).abs().max()) <= 8 * U * float(z64.abs().max())
+        pq = q6[..., a] * q6[..., b] * torch.where(a == b, 1.0, 2.0)
+        den = (pq * z64).sum(-1, keepdim=True)
+        num = (pq[..., None] * S64).sum(2)
+        ref = torch.where(den > 0, num / den, torch.zeros_like(num))
+        tol = (n / 32 + 64) * U
+        bound = tol * ((pq.abs()[..., None] * S64.abs()).sum(2) / den.abs() + ref.abs() *
+                       (pq.abs() * z64.abs()).sum(-1, keepdim=True) / den.abs())
+        sure = den.abs() > 1e-3 * (pq.abs() * z64.abs()).sum(-1, keepdim=True)
+        assert bool((((out.double() - ref).abs() <= bound + 1e-30) | ~sure).all())
