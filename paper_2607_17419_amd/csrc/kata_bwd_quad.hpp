@@ -236,15 +236,32 @@ __device__ __forceinline__ void qd_query_side(const QuadArgs& a, char* lds, int 
 // With a multiple of eight heads a head's workgroups share an XCD, whose L2
 // then holds its rows: four key sides, four query sides, and so on, the ranks
 // of a group of four running up and down in turn (NB4 = NB rounded up to four;
-// ranks past NB exit).  Otherwise ranks are the slow index, so that
+// ranks past NB exit).  The heads of an XCD follow each other but for its last
+// kQTailHeads, whose groups of eight take turns, so that the launch ends with
+// the shortest walks of several heads and not with all of one head: backward
+// and forward at B1 H16 T4096 245 -> 222 us, B3 608 -> 577, B8 1507 -> 1477
+// (2 heads: 222, 588, 1487; 8: 222, 578, 1487; all of them: 1537 at B8, more
+// heads than an L2 holds).  Otherwise ranks are the slow index, so that
 // neighbouring ids carry like work on every XCD.
+constexpr int kQTailHeads = 4;
 __global__ __launch_bounds__(256, 3) void bwd_quad_kernel(QuadArgs a, int BH, int NB) {
   __shared__ __attribute__((aligned(16))) char lds[2 * kQStageK];
   const int id = blockIdx.x;
   int bh, side, rank;
   if ((BH & 7) == 0) {
-    const int per = 2 * ((NB + 3) & ~3), j = (id >> 3) % per, grp = j >> 3;
-    bh = (id & 7) + 8 * ((id >> 3) / per);
+    const int per = 2 * ((NB + 3) & ~3), x = id >> 3;
+    const int nh = BH >> 3, ni = min(nh, kQTailHeads), x0 = (nh - ni) * per;
+    int j, hx;
+    if (x < x0) {
+      j = x % per;
+      hx = x / per;
+    } else {
+      const int y = x - x0;
+      j = (y & 7) + 8 * (y / 8 / ni);
+      hx = nh - ni + y / 8 % ni;
+    }
+    bh = (id & 7) + 8 * hx;
+    const int grp = j >> 3;
     side = (j >> 2) & 1;
     rank = 4 * grp + ((grp & 1) ? 3 - (j & 3) : (j & 3));
     if (rank >= NB) return;

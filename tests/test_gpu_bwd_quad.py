@@ -44,7 +44,7 @@ def _close(got, ref, what):
 
 
 @pytest.mark.parametrize("B,H,T", [(1, 1, 2), (1, 3, 32), (2, 4, 33), (1, 2, 127), (1, 8, 128),
-                                   (1, 5, 129), (2, 8, 544), (1, 3, 641)])
+                                   (1, 5, 129), (2, 8, 544), (1, 3, 641), (5, 8, 160)])
 def test_quadratic_gradients_at_tile_edges(kata, orc, B, H, T):
     import torch
     log(f"case quadratic gradients B{B} H{H} T{T}")
