@@ -530,11 +530,12 @@ void by_width(int w, F&& f) {
 // the chunk states' with T n dv, n = d(d+1)/2.  Forward, measured with eight heads
 // (us, quadratic : chunk states): d = dv = 64 T16384 2990 : 20290; 32 T8192
 // 270 : 1170; 24 T8192 430 : 514; 16 T8192 204 : 239; 7 and 5 T4096 62 : 67; at
-// T1000 28 : 2990, 27 : 185 (24 and 40), 16 : 31 (7 and 5).
+// T1000 28 : 2990, 27 : 185 (24 and 40), 16 : 31 (7 and 5).  A launch holds fewer
+// than 2^32 threads: calls of more tokens keep the chunk states' two-dimensional grids.
 bool quad32_fwd_ok(int BH, int T, int d, int g) {
   const int n = d * (d + 1) / 2;
   return g == 1 && (T <= 4096 || (T <= 65536 && T <= 30 * n)) &&
-         static_cast<long long>(BH) * ((T + 31) / 32) < (1LL << 31);
+         static_cast<long long>(BH) * ((T + 31) / 32) * 64 * kW32 < (1LL << 32);
 }
 // Gradients, eight heads: d = dv = 64 T8192 2527 : 4054, T16384 9813 : 8158; 32 T8192
 // 1153 : 1600; 16 T8192 819 : 924; one head T8192 404 : 1049; widths that are
@@ -542,7 +543,7 @@ bool quad32_fwd_ok(int BH, int T, int d, int g) {
 bool quad32_bwd_ok(int BH, int T, int d, int dv, int g) {
   const auto whole = [](int w) { return w == 16 || w == 32 || w == 64; };
   return g == 1 && dv <= 64 && T <= (whole(d) && whole(dv) ? 8192 : 4096) &&
-         static_cast<long long>(BH) * ((T + 127) / 128) * 8 < (1LL << 31);
+         static_cast<long long>(BH) * ((T + 127) / 128) * 8 * 64 * kW32 < (1LL << 32);
 }
 
 template <typename Tin>

@@ -117,3 +117,24 @@ def test_against_chunk_states(kata, d, dv, T):
     for name, x, y in zip(("dq", "dk", "dv"), a, b):
         assert float((cut(x) - y).norm() / y.norm()) <= 2e-5, name
         assert not x[:, :, T:].any() or name == "dq"
+
+
+def test_more_tokens_than_one_launch_holds(kata):
+    """65535 heads of 2100 tokens: the pair tiles would need 2^32 threads or more
+    in one launch, so the chunk states form these gradients; the first and the
+    last heads equal the same heads by themselves (quadratic form)."""
+    import torch
+    BH, T, d, dv = 65535, 2100, 7, 5
+    assert BH * -(-T // 128) * 8 * 512 >= 1 << 32
+    log(f"case fp32 gradients B{BH} H1 T{T} d{d} dv{dv}")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, g = (torch.randn((BH, 1, T, w), generator=gen, device="cuda") for w in (d, d, dv, dv))
+    g[:, :, :32] = 0  # rows whose few weights may nearly vanish
+    out = kata.fwd_chunked(q, k, v, 32)
+    grads = kata.bwd_chunked(q, k, v, out, g, 32)
+    torch.cuda.synchronize()
+    for part in (slice(0, 2), slice(BH - 2, BH)):
+        cut = [x[part].contiguous() for x in (q, k, v, out, g)]
+        alone = kata.bwd_chunked(*cut, 32)
+        for name, x, y in zip(("dq", "dk", "dv"), grads, alone):
+            assert float((x[part] - y).norm() / y.norm()) <= 2e-5, name
