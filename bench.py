@@ -612,8 +612,7 @@ def bench_backward(kata, dev, hip, Ts=(1024, 2048, 4096, 8192), steps=5, warmup=
         g2 = torch.Generator(device=dev)
         g2.manual_seed(7)
         dout = torch.randn(B, H, T, dv, device=dev, generator=g2)
-        span = kata.default_span(B, H, T, d, dv, C, kata.KATA_BF16)
-        fws = torch.empty(kata.workspace_bytes(B, H, T, d, dv, C, kata.KATA_BF16, span),
+        fws = torch.empty(kata.workspace_bytes(B, H, T, d, dv, C, kata.KATA_BF16),
                           dtype=torch.uint8, device=dev)
         bws = torch.empty(kata.bwd_workspace_bytes(B, H, T, d, dv, C, 1, kata.KATA_BF16),
                           dtype=torch.uint8, device=dev)
@@ -627,8 +626,7 @@ def bench_backward(kata, dev, hip, Ts=(1024, 2048, 4096, 8192), steps=5, warmup=
 
         def train_step(i):
             fev.record(2 * i, stream)
-            kata.fwd_chunked_train(q, k, v, C, span_chunks=span, out=out, den=den,
-                                   workspace=fws)
+            kata.fwd_chunked_train(q, k, v, C, out=out, den=den, workspace=fws)
             fev.record(2 * i + 1, stream)
             kata.bwd_chunked(q, k, v, out, dout, C, 1, workspace=bws, events=bev.block(7 * i),
                              grads=grads, den=den)
