@@ -52,7 +52,7 @@ __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r >> 2) + 4 *
 
 // The rows of one head of q, k, v or a: T rows of w values, taken as WP values
 // padded with zeros, through buffer loads whose range ends at the last row, so
-// that rows past it read as zero and the loads of a tile share one address
+// that rows past it read as zero and the loads of a tile share an address
 // register.  EX: w = WP, half rows in 16-byte pieces; otherwise one value at a
 // time.
 template <typename Tin, int WP, bool EX>
@@ -63,12 +63,12 @@ struct HeadRows {
   __device__ __forceinline__ HeadRows(const Tin* p, int T, int w_)
       : rs(__builtin_amdgcn_make_buffer_rsrc(const_cast<Tin*>(p), 0, T * w_ * SZ, 0x00020000)),
         w(EX ? WP : w_), rb((EX ? WP : w_) * SZ) {}
-  __device__ __forceinline__ float load(int vo, int so) const {
+  __device__ __forceinline__ float load(int vo) const {
     if constexpr (SZ == 4)
-      return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, vo, so, 0));
+      return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, vo, 0, 0));
     else
       return __uint_as_float(static_cast<uint32_t>(static_cast<uint16_t>(
-                                 __builtin_amdgcn_raw_buffer_load_b16(rs, vo, so, 0))) << 16);
+                                 __builtin_amdgcn_raw_buffer_load_b16(rs, vo, 0, 0))) << 16);
   }
   // This lane's half (h) of a row.
   __device__ __forceinline__ void half(int row, int h, float (&x)[WP / 2]) const {
@@ -92,19 +92,24 @@ struct HeadRows {
     } else {
       const int left = w - h * (WP / 2);  // values past the row: out of range, zero
 #pragma unroll
-      for (int i = 0; i < WP / 2; ++i) x[i] = load(i < left ? vo + i * SZ : -SZ, 0);
+      for (int i = 0; i < WP / 2; ++i) x[i] = load(i < left ? vo + i * SZ : -SZ);
     }
   }
   // Column j of rows r0 + acc_row(r, h).  Columns past w give another column:
-  // they only reach result rows that are not stored.
+  // they only reach result rows that are not stored.  The row is in the vector
+  // offset throughout: the range check that makes rows past T - 1 read as zero
+  // is specified for that offset (with the instruction's own), not for the
+  // scalar one.
   __device__ __forceinline__ void column(int j, int r0, int h, float (&x)[16]) const {
-    const int vo = (r0 + 4 * h) * rb + min(j, w - 1) * SZ;
+    int vo = (r0 + 4 * h) * rb + min(j, w - 1) * SZ;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      if constexpr (EX)
-        x[r] = load(vo + (8 * ((r >> 2) & 1) + (r & 3)) * WP * SZ, 16 * (r >> 3) * WP * SZ);
-      else
-        x[r] = load(vo, (8 * (r >> 2) + (r & 3)) * rb);
+      if constexpr (EX) {
+        x[r] = load(vo + (8 * (r >> 2) + (r & 3)) * WP * SZ);
+      } else {
+        x[r] = load(vo);
+        vo += (r & 3) == 3 ? 5 * rb : rb;
+      }
     }
   }
 };

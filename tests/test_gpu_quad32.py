@@ -138,3 +138,33 @@ def test_more_tokens_than_one_launch_holds(kata):
         alone = kata.bwd_chunked(*cut, 32)
         for name, x, y in zip(("dq", "dk", "dv"), grads, alone):
             assert float((x[part] - y).norm() / y.norm()) <= 2e-5, name
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,dv", [(16, 16), (64, 64), (7, 5), (33, 30), (64, 200)])
+def test_reads_stay_inside_a_head(kata, dtype, d, dv):
+    """A head between two whose every value is NaN: rows past its T (or before its
+    first) that were read from them would show, even with weight zero.  T below
+    and above the 16 and 28 rows that a tile's later loads lie past its first."""
+    import torch
+    for T in (1, 5, 10, 20, 27, 28, 33, 45):
+        log(f"case fp32 quadratic between NaN heads {dtype} T{T} d{d} dv{dv}")
+        ins = _inputs(dtype, 1, 1, T, d, dv)
+        alone = [x.cuda() for x in ins]
+        three = [torch.full((1, 3) + x.shape[2:], float("nan"), dtype=x.dtype, device="cuda")
+                 for x in ins]
+        for x, y in zip(three, alone):
+            x[:, 1:2] = y
+        ref = kata.fwd_chunked(*alone[:3], 32)
+        got = kata.fwd_chunked(*three[:3], 32)
+        torch.cuda.synchronize()
+        assert torch.isfinite(ref).all() and torch.equal(got[:, 1:2], ref), (T, "o")
+        if dv > 64:
+            continue  # the gradients of wide values are not formed quadratically
+        out = torch.full_like(three[3], float("nan"))
+        out[:, 1:2] = ref
+        refs = kata.bwd_chunked(*alone[:3], ref, alone[3], 32)
+        gots = kata.bwd_chunked(*three[:3], out, three[3], 32)
+        torch.cuda.synchronize()
+        for name, x, y in zip(("dq", "dk", "dv"), gots, refs):
+            assert torch.isfinite(y).all() and torch.equal(x[:, 1:2], y), (T, name)
