@@ -7,8 +7,8 @@
 // through chunk states (n = d(d+1)/2), equal near T = 4200 at d = dv = 64, and it
 // runs entirely in matrix instructions, where the chunk output reads a 2080 x
 // 64 state per chunk into scalar products.  B1 H8 T1000 d64 fp32: forward 2990 ->
-// 28 us, coefficients 15 us and gradients 59 us where the backward took 1045;
-// B8 H16 T2048: forward 40.7 -> 1.05 ms (66 TFLOP/s of the 154 that a large fp32
+// 22 us, coefficients and gradients 66 us where the backward took 1045;
+// B8 H16 T2048: forward 40.7 -> 0.60 ms (114 TFLOP/s of the 154 that a large fp32
 // library product reaches), backward 16.3 -> 3.1 ms.
 //
 // A workgroup owns one tile of 32 queries (keys); its eight waves take the
@@ -95,6 +95,10 @@ struct HeadRows {
       for (int i = 0; i < WP / 2; ++i) x[i] = load(i < left ? vo + i * SZ : -SZ);
     }
   }
+  // Column j of one row (columns past w as in column()).
+  __device__ __forceinline__ float at(int j, int row) const {
+    return load(row * rb + min(j, w - 1) * SZ);
+  }
   // Column j of rows r0 + acc_row(r, h).  Columns past w give another column:
   // they only reach result rows that are not stored.  The row is in the vector
   // offset throughout: the range check that makes rows past T - 1 read as zero
@@ -102,6 +106,7 @@ struct HeadRows {
   // scalar one.
   __device__ __forceinline__ void column(int j, int r0, int h, float (&x)[16]) const {
     int vo = (r0 + 4 * h) * rb + min(j, w - 1) * SZ;
+    if constexpr (!EX) asm("" : "+v"(vo));  // else a loop keeps all sixteen offsets in registers
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       if constexpr (EX) {
@@ -121,11 +126,57 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
+// Orders this wave's LDS accesses before and after it (other waves take no part).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int KP>
 __device__ __forceinline__ f32x16 dot_tile(const float (&a)[KP], const float (&b)[KP], f32x16 c) {
 #pragma unroll
   for (int i = 0; i < KP; ++i) c = mf2(a[i], b[i], c);
   return c;
+}
+
+// acc += column j of the 32 rows of X from r0 on (x: this lane's, rows
+// acc_row(r, h)) times the masked diagonal tile w, whose pairs of row and column
+// c count where kUpTo ? row <= c : row >= c and are zero elsewhere.  A zero weight
+// does not hide a non-finite x (0 Inf = NaN): a tile that has one adds its rows
+// one at a time and keeps the sums of the columns that do not take the row, so
+// that a non-finite value reaches the outputs that its pairs belong to and no
+// others.  One wave of the workgroup has the diagonal tile: the weights pass
+// through LDS (kDiagLds), the loop is kept rolled and x is read again, so that
+// this path costs the other no registers (unrolled, with the weights in
+// registers, it took 92 more in the forward at d = dv = 64).
+constexpr int kDiagLds = 1024;  // floats from here on, past reduce_columns' own
+template <bool kUpTo, typename Rows>
+__device__ __forceinline__ void diagonal_products(const Rows& X, int j, int r0,
+                                                  const float (&x)[16], const f32x16& w,
+                                                  f32x16& acc, int c, int h, float* red) {
+  float bad = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) bad += x[r] - x[r];  // 0, or NaN
+  if (!__any(!(bad == 0.f))) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc = mf2(x[r], w[r], acc);
+    return;
+  }
+  float* tile = red + kDiagLds;
+  wave_lds_sync();  // the last call's reads
+#pragma unroll
+  for (int r = 0; r < 16; ++r) tile[r * 64 + 32 * h + c] = w[r];
+  wave_lds_sync();
+#pragma unroll 1
+  for (int row = 0; row < 32; ++row) {
+    const float xr = X.at(j, r0 + row);
+    const float wr = tile[(4 * (row >> 3) + (row & 3)) * 64 + 32 * ((row >> 2) & 1) + c];
+    const f32x16 sum = mf2(h ? 0.f : xr, h ? 0.f : wr, acc);
+    const bool taken = kUpTo ? row <= c : row >= c;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = taken ? sum[e] : acc[e];
+  }
 }
 
 // Adds the eight waves' tiles acc (result row j, column c) in wave order and
@@ -222,23 +273,15 @@ __global__ __launch_bounds__(64 * kW32) void quad32_fwd(const Tin* __restrict__ 
   for (int m = 0; m < NT; ++m) acc[m] = zero16();
   float D = 0.f;
   if (wv <= qt) K.half(32 * wv + c, h, kf);
-  for (int kt = wv; kt <= qt; kt += kW32) {
+  int kt = wv;
+  for (; kt < qt; kt += kW32) {
     f32x16 s = dot_tile(kf, qf, zero16());
-    if (qt == 0) put_early<true>(s, early_scores(q + hb * d, k + hb * d, T, d, lane), c, h);
     K.half(32 * min(kt + kW32, qt) + c, h, kf);  // the next key rows, under the value products
     float part = 0.f;
-    if (kt < qt) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] *= s[r];
-        part += s[r];
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = acc_row(r, h) <= c ? s[r] * s[r] : 0.f;
-        part += s[r];
-      }
+    for (int r = 0; r < 16; ++r) {
+      s[r] *= s[r];
+      part += s[r];
     }
     D += part;
 #pragma unroll
@@ -247,6 +290,27 @@ __global__ __launch_bounds__(64 * kW32) void quad32_fwd(const Tin* __restrict__ 
       V.column(32 * m + c, 32 * kt, h, vc);
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[m] = mf2(vc[r], s[r], acc[m]);
+    }
+  }
+  // The diagonal tile: keys past the query (and past T) are masked.  Apart from the
+  // loop, whose tiles then carry no test and no early scores: 124 registers where a
+  // loop over both took 149, and two workgroups on a CU for one (d = dv = 64, eight
+  // heads of 1024 27 -> 22 us, 128 of 2048 1.04 -> 0.60 ms).
+  if (kt == qt) {
+    f32x16 s = dot_tile(kf, qf, zero16());
+    if (qt == 0) put_early<true>(s, early_scores(q + hb * d, k + hb * d, T, d, lane), c, h);
+    float part = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = acc_row(r, h) <= c ? s[r] * s[r] : 0.f;
+      part += s[r];
+    }
+    D += part;
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      float vc[16];
+      V.column(32 * m + c, 32 * kt, h, vc);
+      diagonal_products<true>(V, 32 * m + c, 32 * kt, vc, s, acc[m], c, h, red);
     }
   }
   reduce_columns(red, D, tot);
@@ -410,7 +474,11 @@ __global__ __launch_bounds__(64 * kW32) void quad32_grad(
     for (int m = 0; m < ND; ++m) dka[m] = zero16();
 #pragma unroll
     for (int m = 0; m < NV; ++m) dva[m] = zero16();
-    for (int qt = kt + wv; qt < NQ; qt += kW32) {
+    // the diagonal tile apart from the others: 161 registers for the 16-wide
+    // form in place of 191, 24.5 : 25.2 us (T1024, eight heads), 65.7 : 66.6 at d = dv
+    // = 64; the query side too: 23.8 and 67.7 us
+    auto tile = [&](int qt, auto diagonal) __attribute__((always_inline)) {
+      constexpr bool kDiag = decltype(diagonal)::value;
       const int r0 = 32 * qt;
       Q.half(r0 + c, h, x);
       A.half(r0 + c, h, y);
@@ -419,7 +487,7 @@ __global__ __launch_bounds__(64 * kW32) void quad32_grad(
       for (int r = 0; r < 16; ++r) cw[r] = bhp[min(r0 + acc_row(r, h), T - 1)];
       f32x16 s = dot_tile(x, kf, zero16());
       cw = dot_tile(y, vf, cw);
-      if (qt == 0) {
+      if (kDiag && qt == 0) {
         put_early<false>(s, early_scores(q + hb * d, k + hb * d, T, d, lane), c, h);
         put_early<false>(cw, early_c<Tin, VP, EX>(v + hb * dv, a + hb * dv, o + hb * dv, T, dv, lane),
                       c, h);
@@ -428,7 +496,7 @@ __global__ __launch_bounds__(64 * kW32) void quad32_grad(
           s[0] = c00[2 * bh + 1];
         }
       }
-      if (qt > kt && r0 + 32 <= T) {
+      if (!kDiag && r0 + 32 <= T) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           cw[r] *= s[r];  // c_ti s_ti
@@ -447,6 +515,10 @@ __global__ __launch_bounds__(64 * kW32) void quad32_grad(
       for (int m = 0; m < ND; ++m) {
         float col[16];
         Q.column(32 * m + c, r0, h, col);
+        if constexpr (kDiag) {
+          diagonal_products<false>(Q, 32 * m + c, r0, col, cw, dka[m], c, h, red);
+          continue;
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) dka[m] = mf2(col[r], cw[r], dka[m]);
       }
@@ -454,10 +526,16 @@ __global__ __launch_bounds__(64 * kW32) void quad32_grad(
       for (int m = 0; m < NV; ++m) {
         float col[16];
         A.column(32 * m + c, r0, h, col);
+        if constexpr (kDiag) {
+          diagonal_products<false>(A, 32 * m + c, r0, col, s, dva[m], c, h, red);
+          continue;
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) dva[m] = mf2(col[r], s[r], dva[m]);
       }
-    }
+    };
+    if (wv == 0) tile(kt, std::true_type{});
+    for (int qt = kt + (wv == 0 ? kW32 : wv); qt < NQ; qt += kW32) tile(qt, std::false_type{});
     const int nc = min(32, T - 32 * kt);
 #pragma unroll
     for (int m = 0; m < ND; ++m)
@@ -502,6 +580,10 @@ __global__ __launch_bounds__(64 * kW32) void quad32_grad(
       for (int m = 0; m < ND; ++m) {
         float col[16];
         K.column(32 * m + c, r0, h, col);
+        if (kt == qt) {
+          diagonal_products<true>(K, 32 * m + c, r0, col, cw, dqa[m], c, h, red);
+          continue;
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) dqa[m] = mf2(col[r], cw[r], dqa[m]);
       }

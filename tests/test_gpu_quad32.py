@@ -168,3 +168,75 @@ def test_reads_stay_inside_a_head(kata, dtype, d, dv):
         torch.cuda.synchronize()
         for name, x, y in zip(("dq", "dk", "dv"), gots, refs):
             assert torch.isfinite(y).all() and torch.equal(x[:, 1:2], y), (T, name)
+
+
+def _causal(q, k, v, g, o=None):
+    """Outputs and gradients (of the given o, or their own), each a sum over its own
+    pairs i <= t alone, with the sums of the terms' magnitudes: one head, float64."""
+    q, k, v, g = (x[0, 0].double().numpy() for x in (q, k, v, g))
+    T = len(q)
+    S = [[q[t] @ k[i] for i in range(t + 1)] for t in range(T)]
+    D = np.array([sum(s * s for s in S[t]) for t in range(T)])
+    inv = np.array([1.0 / x if x > 0 else 0.0 for x in D])
+    own, om = np.zeros_like(v), np.zeros_like(v)
+    for t in range(T):
+        for i in range(t + 1):
+            own[t] += S[t][i] ** 2 * v[i] * inv[t] if D[t] > 0 else 0.0
+            om[t] += (np.abs(q[t]) @ np.abs(k[i])) ** 2 * np.abs(v[i]) * inv[t]
+    o = own if o is None else o[0, 0].double().numpy()
+    vals = [own] + [np.zeros_like(x) for x in (q, k, v)]
+    mags = [om] + [np.zeros_like(x) for x in (q, k, v)]
+    ab = np.abs
+    for t in range(T):
+        a = g[t] * inv[t]
+        b = -(g[t] @ o[t]) * inv[t]
+        for i in range(t + 1):
+            c = a @ v[i] + b
+            cm = ab(a) @ ab(v[i]) + ab(g[t]) @ ab(o[t]) * inv[t]
+            sm = ab(q[t]) @ ab(k[i])
+            vals[1][t] += 2 * c * S[t][i] * k[i]
+            vals[2][i] += 2 * c * S[t][i] * q[t]
+            vals[3][i] += S[t][i] ** 2 * a
+            mags[1][t] += 2 * cm * sm * ab(k[i])
+            mags[2][i] += 2 * cm * sm * ab(q[t])
+            mags[3][i] += sm * sm * ab(a)
+    return vals, mags
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("d,dv", [(16, 16), (64, 64), (33, 30), (24, 200)])
+def test_non_finite_values_stay_causal(kata, dtype, bad, d, dv):
+    """One non-finite entry of v, k, q or dout: the outputs that its pairs belong to
+    are not finite, and every other output is right.  Row 5 is among the rows with
+    fp64 scores, 20 in the first tile, 50 in the second of three."""
+    import torch
+    T = 70
+    for t0 in (5, 20, 50):
+        clean = _inputs(dtype, 1, 1, T, d, dv, seed=t0)
+        with np.errstate(all="ignore"):
+            o = torch.from_numpy(_causal(*clean)[0][0].astype(np.float32))[None, None]
+        for which, name in enumerate(("q", "k", "v", "dout")):
+            if dv > 64 and name not in ("k", "v"):
+                continue
+            log(f"case fp32 quadratic {dtype} d{d} dv{dv}: {bad} in {name} at row {t0}")
+            ins = [x.clone() for x in clean]
+            ins[which][0, 0, t0, 1] = bad
+            with np.errstate(all="ignore"):
+                vals, mags = _causal(*ins, o=o)
+            qd, kd, vd, gd, od = (x.cuda() for x in (*ins, o))
+            got = [kata.fwd_chunked(qd, kd, vd, 32)]
+            if dtype == "bf16" and d == dv == 64:  # the bf16 matrix-core forward
+                got = [torch.from_numpy(vals[0])[None, None]]
+            if dv <= 64:
+                got += kata.bwd_chunked(qd, kd, vd, od, gd, 32)
+            torch.cuda.synchronize()
+            for what, x, ref, mag in zip(("o", "dq", "dk", "dv"), got, vals, mags):
+                x = x[0, 0].double().cpu().numpy()
+                fin = np.isfinite(ref)
+                assert np.array_equal(np.isfinite(x), fin), (name, t0, what)
+                assert fin[:t0 if name in ("k", "v") and what in ("o", "dq") else 0].all()
+                # a finite output without a finite bound is the zero of D_t = NaN
+                mag = np.where(np.isfinite(mag), mag, 0.0)[fin]
+                assert np.all(np.abs(x[fin] - ref[fin]) <= _tol(T, d, dv) * mag + 1e-30), (
+                    name, t0, what)
