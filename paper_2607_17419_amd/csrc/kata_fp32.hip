@@ -593,21 +593,18 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_f32(
 #pragma unroll
     for (int u = 0; u < kWideUnroll; ++u) {
       const int f = f0 + u * rows;
-      const bool in = f < n;
-      const float2 p = pkq[in ? f : n - 1];
+      if (f >= n) continue;  // its load read row n - 1 again
+      const float2 p = pkq[f];
       s[u].x += p.x * vv[0];
       s[u].y += p.x * vv[1];
       s[u].z += p.x * vv[2];
       s[u].w += p.x * vv[3];
-      if (in) {
-        if constexpr (NT) stream_store4(Sh + f * dv, s[u]);
-        else *reinterpret_cast<float4*>(Sh + f * dv) = s[u];
-      }
-      const float w = in ? p.y : 0.f;
-      num[0] += w * s[u].x;
-      num[1] += w * s[u].y;
-      num[2] += w * s[u].z;
-      num[3] += w * s[u].w;
+      if constexpr (NT) stream_store4(Sh + f * dv, s[u]);
+      else *reinterpret_cast<float4*>(Sh + f * dv) = s[u];
+      num[0] += p.y * s[u].x;
+      num[1] += p.y * s[u].y;
+      num[2] += p.y * s[u].z;
+      num[3] += p.y * s[u].w;
     }
   }
   float den = 0.f;

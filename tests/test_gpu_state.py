@@ -118,3 +118,24 @@ def test_decode_step_forms(kata, dtype, B, H, d, dv, g):
                        (pq.abs() * z64.abs()).sum(-1, keepdim=True) / den.abs())
         sure = den.abs() > 1e-3 * (pq.abs() * z64.abs()).sum(-1, keepdim=True)
         assert bool((((out.double() - ref).abs() <= bound + 1e-30) | ~sure).all())
+
+
+@pytest.mark.parametrize("d,dv", [(64, 64), (32, 64), (24, 16), (5, 4)])
+def test_decode_infinite_state_entry(kata, d, dv):
+    """An infinity in the state's last row (which threads past the last row load
+    again) reaches its own output column as an infinity, and no other column."""
+    import torch
+    log(f"case decode, infinity in the last state row: B1 H2 d{d} dv{dv}")
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    n = d * (d + 1) // 2
+    S = torch.randn((1, 2, n, dv), generator=gen, device="cuda")
+    z = torch.rand((1, 2, n), generator=gen, device="cuda") + 1.0
+    q, k = (torch.rand((1, 2, d), generator=gen, device="cuda") + 0.1 for _ in range(2))
+    v = torch.randn((1, 2, dv), generator=gen, device="cuda")
+    clean = kata.decode_step(S.clone(), z.clone(), q, k, v)
+    S[0, 1, n - 1, 2] = float("inf")
+    out = kata.decode_step(S, z, q, k, v)  # all weights and z positive
+    torch.cuda.synchronize()
+    assert float(out[0, 1, 2]) == float("inf")
+    clean[0, 1, 2] = float("inf")
+    assert torch.equal(out, clean)
