@@ -717,7 +717,9 @@ hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const
   const int n = g * ((d / g) * (d / g + 1) / 2);
   const size_t head = static_cast<size_t>(n) * dv * sizeof(float), state = head * BH;
   const bool pow2 = dv >= 4 && dv <= 256 && (dv & (dv - 1)) == 0;
-  if (pow2 && (state <= (140u << 20) || head <= (160u << 10))) {
+  // A launch holds fewer than 2^32 threads: 256 per head serve four times as many heads.
+  const bool fits = static_cast<long long>(BH) * kWideThreads < (1LL << 32);
+  if (pow2 && fits && (state <= (140u << 20) || head <= (160u << 10))) {
     const unsigned m = d / g, inv_m = ((1u << 20) + m - 1) / m;  // exact quotients below 64 m
     auto go = [&](auto nt) {
       decode_wide_f32<Tin, decltype(nt)::value><<<BH, kWideThreads, 0, st>>>(

@@ -139,3 +139,27 @@ def test_decode_infinite_state_entry(kata, d, dv):
     assert float(out[0, 1, 2]) == float("inf")
     clean[0, 1, 2] = float("inf")
     assert torch.equal(out, clean)
+
+
+def test_decode_of_more_heads_than_a_wide_launch_holds(kata):
+    """2^22 + 8 small heads: 1024 threads each would be 2^32 or more in one launch.
+    The first and the last heads equal the same heads by themselves."""
+    import torch
+    BH, d, dv = (1 << 22) + 8, 1, 4
+    log(f"case decode B{BH} H1 d{d} dv{dv}")
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    S = torch.randn((BH, 1, 1, dv), generator=gen, device="cuda")
+    z = torch.rand((BH, 1, 1), generator=gen, device="cuda")
+    q, k = (torch.randn((BH, 1, d), generator=gen, device="cuda") for _ in range(2))
+    v = torch.randn((BH, 1, dv), generator=gen, device="cuda")
+    ends = (slice(0, 3), slice(BH - 3, BH))
+    alone = []
+    for part in ends:
+        S1, z1 = S[part].clone(), z[part].clone()
+        out = kata.decode_step(S1, z1, *(x[part].clone() for x in (q, k, v)))
+        alone.append((out, S1, z1))
+    out = kata.decode_step(S, z, q, k, v)
+    torch.cuda.synchronize()
+    for part, refs in zip(ends, alone):
+        for x, y in zip((out, S, z), refs):  # one product and one sum, or their quotient
+            assert torch.allclose(x[part], y, rtol=8 * U, atol=0)
