@@ -717,9 +717,18 @@ hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const
   const int n = g * ((d / g) * (d / g + 1) / 2);
   const size_t head = static_cast<size_t>(n) * dv * sizeof(float), state = head * BH;
   const bool pow2 = dv >= 4 && dv <= 256 && (dv & (dv - 1)) == 0;
+  // Heads of a few KB leave most of 1024 threads idle and, in large numbers, the
+  // chip with one workgroup per CU (us, wide : 256 threads, fp32): d 8 dv 16 512 heads
+  // 9 : 10, 1024 15 : 13, 16384 209 : 170; d 16 dv 32 (17 KB) 768 heads 14 : 13, 16384
+  // 265 : 235; but d 24 dv 16 (19 KB) 1024 heads 18.5 : 18.9, 16384 280 : 295, d 16 dv
+  // 64 (35 KB) 8192 heads 145 : 166.  For narrow values the 256-thread kernel ends in a
+  // walk over 1024 / dv partial sums: dv 8 1024 heads 15.6 : 16.5, 1536 22.4 : 20.9;
+  // dv 4 4096 heads 58 : 65, 16384 227 : 202.
+  const bool few = BH <= max(512, 81920 / (dv * dv));
   // A launch holds fewer than 2^32 threads: 256 per head serve four times as many heads.
   const bool fits = static_cast<long long>(BH) * kWideThreads < (1LL << 32);
-  if (pow2 && fits && (state <= (140u << 20) || head <= (160u << 10))) {
+  if (pow2 && fits && (few || head >= (18u << 10)) &&
+      (state <= (140u << 20) || head <= (160u << 10))) {
     const unsigned m = d / g, inv_m = ((1u << 20) + m - 1) / m;  // exact quotients below 64 m
     auto go = [&](auto nt) {
       decode_wide_f32<Tin, decltype(nt)::value><<<BH, kWideThreads, 0, st>>>(
