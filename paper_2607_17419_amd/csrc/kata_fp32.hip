@@ -53,8 +53,10 @@ __device__ __forceinline__ uint16_t pair_of(int f, int d, int g) {
 //     bits, and the rest); two bf16 MFMAs per tile then add exact products in
 //     fp32.  The vector products and splits, about 56 instructions for four
 //     MFMAs, bound the loop.  A product that overflows fp32 has no such split
-//     (inf - inf): a tile whose sums are not finite is formed again from the
-//     inputs with plain fp32 arithmetic.
+//     (inf - inf), nor has an infinite v against a zero rest: a tile whose sums
+//     are not finite is formed again in fp32, on the matrix cores (B4 H16 T2000
+//     with one NaN in v 0.42 ms, T8192 of one head 1.2 ms; one thread per output
+//     took 5.9 and 1.6 ms, scalar sums per lane here 8 and 30 ms).
 //   fp32 inputs: fp32 MFMAs (v_mfma_f32_32x32x2_f32), whose rate bounds it.
 // B4 H16 T2000 d64 bf16: 5.90 ms with one thread per output and scalar fp32
 // sums, 0.117 ms here.
@@ -264,20 +266,36 @@ __global__ __launch_bounds__(256, NT <= 2 ? (std::is_same<Tin, bf16_t>::value ? 
     for (int m = 0; m < NT; ++m)
 #pragma unroll
       for (int r = 0; r < 16; ++r) worst += acc[m][r] - acc[m][r];  // 0, or NaN
-    if (__any(!(worst == 0.f))) {
-      for (int m = 0; m < NT; ++m)
-        for (int r = 0; r < 16; ++r) {
-          const int fr = 32 * tile + 8 * (r >> 2) + 4 * h + (r & 3), j = 32 * m + c;
-          if (fr >= n || j >= dv) continue;
-          const uint16_t pp = pair_of(fr, d, g);
-          const int a = pp & 0xFF, b = pp >> 8;
-          float s = 0.f;
-          for (long long t = t_begin; t < t_end; ++t)
-            s += (load_f32(kh, t * d + a) * load_f32(kh, t * d + b)) * load_f32(vh, t * dv + j);
-          So[static_cast<long long>(fr) * dv + j] = s;
+    if (__builtin_expect(__any(!(worst == 0.f)), 0)) {
+      // the tile again from the inputs, with fp32 products and sums on the fp32
+      // matrix cores, one token per lane half (z is such a sum already)
+      constexpr int U = NT <= 2 ? 8 : 4;
+#pragma unroll
+      for (int m = 0; m < NT; ++m) acc[m] = f32x16{};
+#pragma unroll 1
+      for (long long t0 = t_begin; t0 < t_end; t0 += 2 * U) {
+        const Tin* kr = kh + t0 * d;
+        const Tin* vr = vh + t0 * dv;
+        const int left = static_cast<int>(min(t_end - t0, static_cast<long long>(2 * U)));
+        float p[U], x[U][NT];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+          const bool in = 2 * e + h < left;
+          const int t = in ? 2 * e + h : 0;
+          p[e] = to_f32(kr[t * d + fa]) * to_f32(kr[t * d + fb]);
+          if (!in) p[e] = 0.f;
+#pragma unroll
+          for (int m = 0; m < NT; ++m) {
+            const float y = to_f32(vr[t * dv + min(32 * m + c, dv - 1)]);
+            x[e][m] = in ? y : 0.f;  // columns past dv are not stored
+          }
         }
-      if (h == 0 && f < n) zo[f] = zacc;
-      return;
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+#pragma unroll
+          for (int m = 0; m < NT; ++m)
+            acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[e], x[e][m], acc[m], 0, 0, 0);
+      }
     }
   }
 #pragma unroll

@@ -165,3 +165,34 @@ def test_decode_of_more_heads_than_a_wide_launch_holds(kata):
     for part, refs in zip(ends, alone):
         for x, y in zip((out, S, z), refs):  # one product and one sum, or their quotient
             assert torch.allclose(x[part], y, rtol=8 * U, atol=0)
+
+
+@pytest.mark.parametrize("H,T,d,dv,g", [(2, 200, 64, 64, 1), (16, 130, 64, 64, 2), (2, 100, 7, 5, 1),
+                                        (1, 100, 64, 256, 1)])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_state_non_finite_inputs(kata, H, T, d, dv, g, bad):
+    """One non-finite entry of v or k gives the infinities and NaN of fp32
+    arithmetic in its own state entries, and the sums elsewhere (one wave and four
+    per tile, both staging forms)."""
+    import torch
+    a, b = (torch.from_numpy(x) for x in _pairs(d, g))
+    for name in ("v", "k"):
+        log(f"case state {bad} in {name}: H{H} T{T} d{d} dv{dv} g{g}")
+        k, v = _inputs("bf16", H, T, d, dv, 9)
+        (v if name == "v" else k)[0, H - 1, 70, 3] = bad
+        S, z = kata.mg_prefill_state(k.cuda(), v.cuda(), g)
+        torch.cuda.synchronize()
+        phi = (k.double()[..., a] * k.double()[..., b])[0]
+        vd = v.double()[0]
+        ref = torch.zeros((H, a.numel(), dv), dtype=torch.float64)
+        mag = torch.zeros_like(ref)
+        for t in range(T):  # not a product of matrices: its order is the library's
+            term = phi[:, t, :, None] * vd[:, t, None, :]
+            ref += term
+            mag += term.abs()
+        for got, r, m in ((S.cpu()[0].double(), ref, mag),
+                          (z.cpu()[0].double(), phi.sum(1), phi.abs().sum(1))):
+            fin = torch.isfinite(r)
+            assert torch.equal(torch.isnan(got), torch.isnan(r))
+            assert torch.equal(got[torch.isinf(r)], r[torch.isinf(r)])
+            assert bool(((got - r).abs()[fin] <= (T + 3) * U * m[fin] + 1e-37).all())
