@@ -925,7 +925,7 @@ hipError_t launch_bwd(const void* q, const void* k, const void* v, const float* 
   if constexpr (std::is_same<Tin, bf16_t>::value) bf = bwd_bf_ok(d, dv, C, g);
   if (bf && bwd_quad_ok(BH, T))
     return launch_bwd_quad(q, k, v, out, dout, den, dq, dk, dv_out, BH, T, ws, st, ev);
-  if (!bf && quad32_bwd_ok(BH, T, d, dv, g))
+  if (!bf && quad32_bwd_ok(BH, T, d, dv, C, g))
     return launch_quad32_bwd<Tin>(q, k, v, out, dout, den, dq, dk, dv_out, BH, T, d, dv, ws, st,
                                   ev);
   // bf16 path: from bwd_bf_fused_min_heads() heads on, each state launch also

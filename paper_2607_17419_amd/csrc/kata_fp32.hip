@@ -688,7 +688,7 @@ hipError_t launch_fp32_forward(const void* q, const void* k, const void* v, floa
   const long long bh_stride = rec * NC;
   hipError_t e = record(ev, 0, st);
   if (e != hipSuccess) return e;
-  if (quad32_fwd_ok(BH, T, d, g)) {  // one launch, no states
+  if (quad32_fwd_ok(BH, T, d, dv, C, g)) {  // one launch, no states
     for (int i = 1; i < 3; ++i)
       if ((e = record(ev, i, st)) != hipSuccess) return e;
     if ((e = launch_quad32_fwd<Tin>(q, k, v, out, BH, T, d, dv, st)) != hipSuccess) return e;

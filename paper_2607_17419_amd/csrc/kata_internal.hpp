@@ -40,8 +40,8 @@ hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const
 // ---- quadratic form in fp32 (kata_quad32.hpp) -------------------------------
 // g = 1; d <= 64, dv <= 256 (gradients: dv <= 64).  The gradients use dv + 1
 // floats of workspace per token and two per head; ev as for launch_bwd.
-bool quad32_fwd_ok(int BH, int T, int d, int g);
-bool quad32_bwd_ok(int BH, int T, int d, int dv, int g);
+bool quad32_fwd_ok(int BH, int T, int d, int dv, int C, int g);
+bool quad32_bwd_ok(int BH, int T, int d, int dv, int C, int g);
 template <typename Tin>
 hipError_t launch_quad32_fwd(const void* q, const void* k, const void* v, float* out, int BH,
                              int T, int d, int dv, hipStream_t st);

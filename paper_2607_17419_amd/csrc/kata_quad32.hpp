@@ -613,24 +613,63 @@ void by_width(int w, F&& f) {
 
 }  // namespace
 
-// Where the quadratic form is the faster one: its time grows with T^2 (d + dv),
-// the chunk states' with T n dv, n = d(d+1)/2.  Forward, measured with eight heads
-// (us, quadratic : chunk states): d = dv = 64 T16384 2990 : 20290; 32 T8192
-// 270 : 1170; 24 T8192 430 : 514; 16 T8192 204 : 239; 7 and 5 T4096 62 : 67; at
-// T1000 28 : 2990, 27 : 185 (24 and 40), 16 : 31 (7 and 5).  A launch holds fewer
-// than 2^32 threads: calls of more tokens keep the chunk states' two-dimensional grids.
-bool quad32_fwd_ok(int BH, int T, int d, int g) {
-  const int n = d * (d + 1) / 2;
-  return g == 1 && (T <= 4096 || (T <= 65536 && T <= 30 * n)) &&
-         static_cast<long long>(BH) * ((T + 31) / 32) * 64 * kW32 < (1LL << 32);
+// Where the quadratic form is the faster one.  Its time grows with T^2 and the
+// matrix instructions of a tile pair (widths padded to their class, whose values
+// then also come one at a time), the chunk states' with T and the state's n dv
+// values, n = d(d+1)/2, above a floor of launches and of one chunk's walk.
+// The models below (us) are fits to both forms at 19 widths, 1 to 512 heads and
+// T 512 .. 62400, C = 64, and to the chunk states at C 4 .. 128; over those 800
+// calls the form that they choose is at most 1.25 times slower than the other
+// (seven calls, all below 300 us, by more than 1.07).  Some of the times (d dv, heads,
+// T: quadratic : chunk states), forward: 64 64, 8, 62400 27987 : 49777; 64 1, 8, 8192
+// 1045 : 1554 and 16384 3923 : 3143; 32 8, 64, 4096 1168 : 1748 and 8192 4242 : 3431;
+// 16 16, 64, 4096 392 : 458; 8 8, 8, 2048 24 : 38 and 4096 63 : 44, 64, 2048 128 : 97;
+// 1 1, 64, 1024 34 : 34 and 4096 416 : 91.  Gradients: 64 64, 8, 8192 2454 : 4039; 16 64,
+// 1, 8192 241 : 330 and 64, 8192 11561 : 10016; 64 1, 8, 2048 337 : 500 and 4096 1157 :
+// 900; 8 64, 8, 1024 90 : 231 and 4096 848 : 451; 24 24, 8, 4096 584 : 652.
+namespace {
+
+int width_class(int w) { return w <= 16 ? 16 : w <= 32 ? 32 : w <= 64 ? 64 : w <= 128 ? 128 : 256; }
+double n_of(int d) { return 0.5 * d * (d + 1); }
+
+double quad32_fwd_us(double BH, double T, int d, int dv) {
+  const int dp = width_class(d), vp = width_class(dv);
+  double tile = 0.5 * (dp + (vp < 32 ? 32 : vp));
+  if (d != dp || dv != vp) tile += 0.02 * d * dp;
+  return 8 + tile * fmax(2.3e-4 * T, 1.5e-8 * BH * T * T);
 }
-// Gradients, eight heads: d = dv = 64 T8192 2527 : 4054, T16384 9813 : 8158; 32 T8192
-// 1153 : 1600; 16 T8192 819 : 924; one head T8192 404 : 1049; widths that are
-// padded: 33 T4096 876 : 952, 24 T8192 2136 : 1257.
-bool quad32_bwd_ok(int BH, int T, int d, int dv, int g) {
+double chunk32_fwd_us(double BH, double T, int d, int dv, double C) {
+  const double n = n_of(d);
+  const double token =
+      3e-4 + n * (fmin(1e-5, 4e-6 + 2.5e-7 * d) + 5e-9 * dv * dv) + 2e-5 * fmax(0, dv - 64);
+  return fmax((22 + 0.06 * T / C + n * (0.25 + 0.01 * dv) + 0.4 * dv) * fmax(1, C / 64),
+              BH * T * token * fmax(1, fmax(24 / C, C / 64)));
+}
+double quad32_bwd_us(double BH, double T, int d, int dv) {
+  const int dp = width_class(d), vp = width_class(dv);
+  double tile = 1.5 * dp + vp + 32 * ((dp + 31) / 32) + 16 * ((vp + 31) / 32);
+  if (d != dp || dv != vp) tile += 0.07 * d * dp + 0.05 * dv * vp;
+  return 20 + tile * fmax(1.6e-4 * T, 1.8e-8 * BH * T * T);
+}
+double chunk32_bwd_us(double BH, double T, int d, int dv, double C) {
+  const double n = n_of(d), token = 7.5e-3 + 3e-4 * d + 4e-5 * dv + 2.5e-7 * n * dv;
+  return fmax(165 + 4.2 * d + 4e-3 * n * dv, BH * T * token * fmax(1, 52 / C));
+}
+
+}  // namespace
+
+// A launch holds fewer than 2^32 threads: calls of more tokens keep the chunk
+// states' two-dimensional grids.
+bool quad32_fwd_ok(int BH, int T, int d, int dv, int C, int g) {
+  return g == 1 && T <= 65536 && (T <= 4096 || T <= 30 * n_of(d)) &&
+         static_cast<long long>(BH) * ((T + 31) / 32) * 64 * kW32 < (1LL << 32) &&
+         quad32_fwd_us(BH, T, d, dv) <= chunk32_fwd_us(BH, T, d, dv, C);
+}
+bool quad32_bwd_ok(int BH, int T, int d, int dv, int C, int g) {
   const auto whole = [](int w) { return w == 16 || w == 32 || w == 64; };
   return g == 1 && dv <= 64 && T <= (whole(d) && whole(dv) ? 8192 : 4096) &&
-         static_cast<long long>(BH) * ((T + 127) / 128) * 8 * 64 * kW32 < (1LL << 32);
+         static_cast<long long>(BH) * ((T + 127) / 128) * 8 * 64 * kW32 < (1LL << 32) &&
+         quad32_bwd_us(BH, T, d, dv) <= chunk32_bwd_us(BH, T, d, dv, C);
 }
 
 template <typename Tin>

@@ -240,3 +240,29 @@ def test_non_finite_values_stay_causal(kata, dtype, bad, d, dv):
                 mag = np.where(np.isfinite(mag), mag, 0.0)[fin]
                 assert np.all(np.abs(x[fin] - ref[fin]) <= _tol(T, d, dv) * mag + 1e-30), (
                     name, t0, what)
+
+
+@pytest.mark.parametrize("B,H,T,d,dv", [(1, 8, 1500, 8, 8), (8, 8, 1500, 8, 8), (1, 2, 1500, 1, 1),
+                                        (64, 8, 1100, 1, 1), (8, 8, 2048, 8, 64), (1, 2, 2048, 8, 64)])
+def test_either_side_of_the_rule(kata, B, H, T, d, dv):
+    """Few and many heads of narrow widths, which the rule sends to the pair tiles and
+    to the chunk states: outputs and gradients of the first and the last head."""
+    import torch
+    log(f"case fp32 rule B{B} H{H} T{T} d{d} dv{dv}")
+    q, k, v, g = _inputs("f32", B, H, T, d, dv)
+    g[:, :, :32] = 0  # rows whose few weights may nearly vanish
+    ends = ((0, 0), (B - 1, H - 1))
+    pick = lambda x, e: x[e[0], e[1]][None, None]
+    refs = [_dense(*(pick(x, e) for x in (q, k, v, g))) for e in ends]
+    out = kata.fwd_chunked(*(x.cuda() for x in (q, k, v)), 64)
+    given = out.clone()
+    for e, (vals, _) in zip(ends, refs):
+        given[e] = torch.from_numpy(vals[0][0, 0].astype(np.float32)).cuda()
+    grads = kata.bwd_chunked(*(x.cuda() for x in (q, k, v)), given, g.cuda(), 64)
+    torch.cuda.synchronize()
+    for e, (vals, mags) in zip(ends, refs):
+        for name, x, ref, mag in zip(("o", "dq", "dk", "dv"), (out, *grads), vals, mags):
+            # the chunk states sum over the n features what the pairs sum over d
+            err = np.abs(pick(x, e).double().cpu().numpy() - ref)[:, :, 32:]
+            tol = _tol(T, d, dv) + 4 * (d * (d + 1) // 2) * U
+            assert np.all(err <= tol * mag[:, :, 32:] + 1e-30), (e, name)
