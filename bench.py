@@ -647,8 +647,10 @@ def bench_backward(kata, dev, hip, Ts=(1024, 2048, 4096, 8192), steps=5, warmup=
               for j, nm in enumerate(names)}
         # with the state and the scan in one launch per record stream, the scan
         # intervals hold no kernel (their event gaps go to the state stages)
-        fused = kata.bwd_fused_scan(B, H, T, d, dv, C, 1, kata.KATA_BF16) == 1
-        if fused:
+        form = kata.bwd_form(B, H, T, d, dv, C, 1, kata.KATA_BF16)
+        quadratic = form == kata.BWD_QUADRATIC  # forms no chunk states: those intervals are empty
+        fused = form == kata.BWD_FUSED_STATES
+        if quadratic or fused:
             st["fwd_states"] += st.pop("prefix_scan")
             st["bwd_states"] += st.pop("suffix_scan")
         fwd_ms = sum(fev.elapsed(2 * i, 2 * i + 1) for i in range(steps)) / steps
@@ -669,16 +671,12 @@ def bench_backward(kata, dev, hip, Ts=(1024, 2048, 4096, 8192), steps=5, warmup=
                 r["mfma_bf16"] = {"achieved": round(tf, 1), "peak": PEAK_BF16_TFLOPS,
                                   "unit": "TFLOP/s", "frac": round(tf / PEAK_BF16_TFLOPS, 4)}
             return r
-        # up to T = 4096 (8192 from eight heads on) the backward forms no chunk
-        # states: its state and scan intervals are empty, and its gradients are
-        # five 64-wide products per causal pair on the matrix cores
-        quadratic = T <= 4096 or (T <= 8192 and B * H >= 8)
         row = {"T": T, "inputs": src, "train_step_ms": round(ms, 3),
                "forward_ms": round(fwd_ms, 3), "backward_ms": round(sum(st.values()), 3),
                "tokens_per_s": B * T / (ms * 1e-3), "quadratic_backward": quadratic,
-               "state_and_scan_fused": fused and not quadratic, "forward_saves_denominators": True,
+               "state_and_scan_fused": fused, "forward_saves_denominators": True,
                "backward_stages_ms": {nm: round(t, 4) for nm, t in st.items()}}
-        if quadratic:
+        if quadratic:  # five 64-wide products per causal pair on the matrix cores
             tf = B * H * T * (T + 1) * 5 * d / (st["gradients"] * 1e-3) / 1e12
             row["gradients_roofline"] = {"bound": "mfma_bf16", "achieved": round(tf, 1),
                                          "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",

@@ -70,9 +70,8 @@ typedef enum { KATA_F32 = 0, KATA_BF16 = 1 } kata_dtype_t;
  *   B, H, T >= 1.  d in 1..64.  dv >= 1.  C >= 1 is the chunk size.
  *   Fast path (bf16 MFMA): dtype = KATA_BF16, d in {32, 64}, dv = 64,
  *   C a multiple of 32 up to 1024.  Every other shape with d <= 64, dv <= 256
- *   and C <= 128 runs on the fp32 path (up to a length that grows with d in the
- *   quadratic form, which needs none of its workspace); anything else is
- *   KATA_ERR_UNSUPPORTED.
+ *   and C <= 128 runs on the fp32 path (with g = 1 in the quadratic form where
+ *   that is faster: kata_fwd_form); anything else is KATA_ERR_UNSUPPORTED.
  *   Workspace (kata_fwd_workspace_bytes) is allocated stream-ordered with
  *   hipMallocAsync on `stream` and released with hipFreeAsync.
  */
@@ -111,8 +110,8 @@ KATA_API size_t kata_noalloc_scratch_bytes(void);
  *                 a span are combined on chip).  0 selects the default
  *                 (kata_fwd_default_span; on the fast path, sequences short
  *                 enough for it to be the faster form are evaluated
- *                 quadratically, with no stored state).  1 is the per-chunk form.  Results do
- *                 not depend on it beyond rounding.
+ *                 quadratically, with no stored state: kata_fwd_form).  1 is the
+ *                 per-chunk form.  Results do not depend on it beyond rounding.
  *   workspace   : device buffer of at least kata_fwd_workspace_bytes(...)
  *                 bytes, 256-byte aligned, owned by the caller, contents
  *                 ignored on entry and undefined on exit.  Two calls in flight
@@ -127,8 +126,9 @@ KATA_API kata_status_t kata_fwd_chunked_ws(const void* q, const void* k, const v
  * kata_fwd_chunked_ws plus stage timing, for profiling: stage_events[0..3]
  * (caller-created HIP events, all non-null) are recorded on `stream` before the
  * state kernel and after each of the three stages (chunk or span state,
- * associative scan, output; the first two are empty in the quadratic form).  Nothing synchronises; the caller reads the
- * elapsed times with hipEventElapsedTime once the stream has reached them.
+ * associative scan, output; the first two are empty in the quadratic form).
+ * Nothing synchronises; the caller reads the elapsed times with
+ * hipEventElapsedTime once the stream has reached them.
  */
 KATA_API kata_status_t kata_fwd_chunked_timed(const void* q, const void* k, const void* v,
                                               float* out, int B, int H, int T, int d, int dv,
@@ -157,8 +157,18 @@ KATA_API kata_status_t kata_fwd_chunked_train_ws(const void* q, const void* k, c
 KATA_API size_t kata_fwd_workspace_bytes(int B, int H, int T, int d, int dv, int C,
                                 kata_dtype_t dtype, int span_chunks);
 
-/* The span (in chunks) that span_chunks = 0 selects for these arguments. */
+/* The span (in chunks) that span_chunks = 0 selects for these arguments where
+ * kata_fwd_form(..., 0) is KATA_FWD_STATES; it also sizes the workspace where it
+ * is not. */
 KATA_API int kata_fwd_default_span(int B, int H, int T, int d, int dv, int C, kata_dtype_t dtype);
+
+/* The form in which a forward of these arguments runs (g = 1: kata_fwd_chunked*,
+ * whose entry points without a span leave it 0; else kata_mg_fwd_chunked*): span or
+ * chunk states, or the quadratic form.  -1 where the arguments are invalid or
+ * unsupported. */
+enum { KATA_FWD_STATES = 0, KATA_FWD_QUADRATIC = 1 };
+KATA_API int kata_fwd_form(int B, int H, int T, int d, int dv, int C, int g, kata_dtype_t dtype,
+                           int span_chunks);
 
 /*
  * The same causal KATA-M1 forward in the quadratic (flash-style) form: the
@@ -348,16 +358,17 @@ KATA_API int kata_lin_default_span(int B, int H, int T, int d, int dv, int C,
  *   ones, about 2e-3 on the test workloads.  Up to T = 4096 (8192 from eight
  *   heads B x H on) those shapes take the quadratic form instead, pair tiles on
  *   the same matrix cores with no chunk states (a_t as a bf16 pair, b_t fp32),
- *   and so do the fp32-arithmetic shapes with g = 1 and dv <= 64 up to T = 4096
- *   (8192 where d and dv are 16, 32 or 64), in fp32.
+ *   and so do the fp32-arithmetic shapes with g = 1 and dv <= 64 where that is
+ *   faster, in fp32, at most up to T = 4096 (8192 where d and dv are 16, 32 or 64):
+ *   kata_bwd_form.
  *   workspace : >= kata_bwd_workspace_bytes(...) bytes, 256-byte aligned,
  *   caller-owned, contents undefined on exit; kata_bwd_chunked allocates it
  *   stream-ordered.  stage_events : 7 caller-created events, recorded before
  *   the first launch and after each of the six (forward states, prefix scan,
  *   per-token coefficients, backward states, suffix scan, gradients); where
- *   kata_bwd_fused_scan() is 1 each state launch also writes the scanned
- *   records and the two scan intervals are empty; the quadratic form leaves
- *   all four state and scan intervals empty.
+ *   kata_bwd_form() is KATA_BWD_FUSED_STATES each state launch also writes the
+ *   scanned records and the two scan intervals are empty; KATA_BWD_QUADRATIC
+ *   leaves all four state and scan intervals empty.
  */
 KATA_API kata_status_t kata_bwd_chunked(const void* q, const void* k, const void* v,
                                         const float* out, const float* dout, float* dq,
@@ -393,8 +404,14 @@ KATA_API kata_status_t kata_bwd_chunked_ex(const void* q, const void* k, const v
                                            hipStream_t stream);
 KATA_API size_t kata_bwd_workspace_bytes(int B, int H, int T, int d, int dv, int C, int g,
                                          kata_dtype_t dtype);
+/* The form in which kata_bwd_chunked* of these arguments runs: chunk states with a
+ * state launch and a scan launch for each record stream, chunk states with both in
+ * one launch, or the quadratic form.  -1 where the arguments are invalid or
+ * unsupported. */
+enum { KATA_BWD_STATES = 0, KATA_BWD_FUSED_STATES = 1, KATA_BWD_QUADRATIC = 2 };
+KATA_API int kata_bwd_form(int B, int H, int T, int d, int dv, int C, int g, kata_dtype_t dtype);
 /* The form of the chunk-state backward for this shape (whether or not its T
- * takes the quadratic form): 1 when it computes the prefix and suffix records
+ * takes the quadratic form, which kata_bwd_form tells): 1 when it computes the prefix and suffix records
  * with the state and the scan in one launch each (bf16 inputs at
  * d = dv = C = 64, g = 1, from 16 heads B x H on), 0 when it runs a state launch
  * and a scan launch for each, -1 for an unsupported shape. */

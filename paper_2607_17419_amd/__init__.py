@@ -29,7 +29,7 @@ KATA_F32, KATA_BF16 = 0, 1
 EXPORTED = (
     "kata_fwd_chunked", "kata_fwd_chunked_ws", "kata_fwd_chunked_timed", "kata_fwd_workspace_bytes",
     "kata_fwd_chunked_train_ws", "kata_bwd_chunked_ex",
-    "kata_fwd_default_span", "kata_fwd_quadratic", "kata_fwd_quadratic_ws",
+    "kata_fwd_default_span", "kata_fwd_form", "kata_fwd_quadratic", "kata_fwd_quadratic_ws",
     "kata_fwd_quadratic_workspace_bytes", "kata_prefill_state", "kata_decode_step",
     "kata_mg_fwd_chunked", "kata_mg_fwd_chunked_ws", "kata_mg_fwd_chunked_timed",
     "kata_mg_fwd_workspace_bytes", "kata_mg_fwd_quadratic_ws",
@@ -37,10 +37,14 @@ EXPORTED = (
     "kata_lin_dim", "kata_lin_fwd_chunked", "kata_lin_fwd_chunked_ws",
     "kata_lin_fwd_chunked_timed", "kata_lin_fwd_workspace_bytes", "kata_lin_default_span",
     "kata_bwd_chunked", "kata_bwd_chunked_ws", "kata_bwd_chunked_timed",
-    "kata_bwd_workspace_bytes", "kata_bwd_fused_scan",
+    "kata_bwd_workspace_bytes", "kata_bwd_fused_scan", "kata_bwd_form",
     "kata_fwd_chunked_noalloc", "kata_noalloc_scratch_bytes",
     "kata_status_string", "kata_abi_version",
 )
+
+# what kata_fwd_form and kata_bwd_form return (-1: unsupported)
+FWD_STATES, FWD_QUADRATIC = 0, 1
+BWD_STATES, BWD_FUSED_STATES, BWD_QUADRATIC = 0, 1, 2
 
 # kata_lin_feature_t
 LIN_IDENTITY, LIN_RELU, LIN_ELU, LIN_LORENTZ, LIN_LORENTZ_S = 0, 1, 2, 3, 4
@@ -81,6 +85,8 @@ def lib():
     L.kata_fwd_workspace_bytes.restype = sz
     L.kata_fwd_default_span.argtypes = [i, i, i, i, i, i, i]
     L.kata_fwd_default_span.restype = i
+    L.kata_fwd_form.argtypes = [i, i, i, i, i, i, i, i, i]
+    L.kata_fwd_form.restype = i
     L.kata_prefill_state.argtypes = [vp, vp, vp, vp, i, i, i, i, i, i, vp]
     L.kata_prefill_state.restype = i
     L.kata_decode_step.argtypes = [vp, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
@@ -138,6 +144,8 @@ def lib():
     L.kata_bwd_workspace_bytes.restype = sz
     L.kata_bwd_fused_scan.argtypes = [i, i, i, i, i, i, i, i]
     L.kata_bwd_fused_scan.restype = i
+    L.kata_bwd_form.argtypes = [i, i, i, i, i, i, i, i]
+    L.kata_bwd_form.restype = i
     L.kata_status_string.argtypes = [i]
     L.kata_status_string.restype = ctypes.c_char_p
     L.kata_abi_version.argtypes = []
@@ -206,6 +214,11 @@ def workspace_bytes(B, H, T, d, dv, C, dtype_code, span_chunks=0) -> int:
 
 def default_span(B, H, T, d, dv, C, dtype_code) -> int:
     return int(lib().kata_fwd_default_span(B, H, T, d, dv, C, dtype_code))
+
+
+def fwd_form(B, H, T, d, dv, C, g, dtype_code, span_chunks=0) -> int:
+    """FWD_STATES, FWD_QUADRATIC, or -1 (kata_fwd_form)."""
+    return int(lib().kata_fwd_form(B, H, T, d, dv, C, g, dtype_code, span_chunks))
 
 
 def fwd_chunked(q, k, v, C: int, span_chunks: int = 0, out=None, workspace=None, stream=None):
@@ -559,8 +572,14 @@ def bwd_workspace_bytes(B, H, T, d, dv, C, g, dtype_code) -> int:
 
 
 def bwd_fused_scan(B, H, T, d, dv, C, g, dtype_code) -> int:
-    """1 when the backward's state launches also scan (kata_bwd_fused_scan)."""
+    """1 when the chunk-state backward's state launches also scan
+    (kata_bwd_fused_scan); bwd_form tells whether a call takes that form."""
     return int(lib().kata_bwd_fused_scan(B, H, T, d, dv, C, g, dtype_code))
+
+
+def bwd_form(B, H, T, d, dv, C, g, dtype_code) -> int:
+    """BWD_STATES, BWD_FUSED_STATES, BWD_QUADRATIC, or -1 (kata_bwd_form)."""
+    return int(lib().kata_bwd_form(B, H, T, d, dv, C, g, dtype_code))
 
 
 def bwd_chunked(q, k, v, out, dout, C: int, g: int = 1, workspace=None, stream=None,

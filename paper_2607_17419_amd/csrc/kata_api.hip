@@ -105,6 +105,16 @@ size_t fwd_workspace_bytes(int B, int H, int T, int d, int dv, int C, int dtype,
   return workspace_for(p, B, H, T, d, dv, C, g, span_chunks);
 }
 
+// The form of a forward (KATA_FWD_* of kata.h, -1); the launches below ask the same
+// predicates.
+int fwd_form(int B, int H, int T, int d, int dv, int C, int g, int dtype, int span_chunks) {
+  const Path p = fwd_path(B, H, T, d, dv, C, dtype, g);
+  if (p == Path::kInvalid || p == Path::kUnsupported || span_chunks < 0) return -1;
+  const bool quad = p == Path::kMfma ? span_chunks == 0 && kata::quad_fwd_ok(B * H, T, d, g)
+                                     : kata::quad32_fwd_ok(B * H, T, d, dv, C, g);
+  return quad ? KATA_FWD_QUADRATIC : KATA_FWD_STATES;
+}
+
 // The quadratic form in place of the span pipeline: the state and scan stages
 // are empty.
 hipError_t quad_staged(const void* q, const void* k, const void* v, float* out, float* den, int BH,
@@ -128,7 +138,7 @@ kata_status_t fwd_ws(const void* q, const void* k, const void* v, float* out, in
   const Path p = fwd_path(B, H, T, d, dv, C, dtype, g);
   if (p == Path::kInvalid) return KATA_ERR_INVALID_ARG;
   if (p == Path::kUnsupported) return KATA_ERR_UNSUPPORTED;
-  const bool by_default = span_chunks == 0;
+  const bool quad = fwd_form(B, H, T, d, dv, C, g, dtype, span_chunks) == KATA_FWD_QUADRATIC;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return KATA_ERR_INVALID_ARG;
   if (span_chunks == 0) span_chunks = default_span(C, d, p);
   if (p == Path::kFp32) span_chunks = 1;
@@ -136,7 +146,7 @@ kata_status_t fwd_ws(const void* q, const void* k, const void* v, float* out, in
   if (workspace_bytes < need) return KATA_ERR_INVALID_ARG;
   const int BH = B * H;
   if (p == Path::kMfma) {
-    if (by_default && kata::quad_fwd_ok(BH, T, d, g))
+    if (quad)
       return from_hip(quad_staged(q, k, v, out, den, BH, T, d, g, stream, ev));
     const int L = span_tokens(T, C, span_chunks);
     if ((static_cast<long long>(T) + L - 1) / L > kGridYZ) return KATA_ERR_UNSUPPORTED;
@@ -466,6 +476,12 @@ int kata_fwd_default_span(int B, int H, int T, int d, int dv, int C, kata_dtype_
   return default_span_of(B, H, T, d, dv, C, dtype, 1);
 }
 
+int kata_fwd_form(int B, int H, int T, int d, int dv, int C, int g, kata_dtype_t dtype,
+                  int span_chunks) {
+  if (!dtype_ok(dtype)) return -1;
+  return fwd_form(B, H, T, d, dv, C, g, dtype, span_chunks);
+}
+
 size_t kata_fwd_workspace_bytes(int B, int H, int T, int d, int dv, int C, kata_dtype_t dtype,
                                 int span_chunks) {
   if (!dtype_ok(dtype)) return 0;
@@ -711,6 +727,12 @@ int kata_bwd_fused_scan(int B, int H, int T, int d, int dv, int C, int g, kata_d
   if (!dtype_ok(dtype)) return -1;
   if (bwd_check(B, H, T, d, dv, C, g, dtype) != KATA_OK) return -1;
   return kata::bwd_fused_scan(B * H, d, dv, C, g, dtype == KATA_BF16) ? 1 : 0;
+}
+
+int kata_bwd_form(int B, int H, int T, int d, int dv, int C, int g, kata_dtype_t dtype) {
+  if (!dtype_ok(dtype)) return -1;
+  if (bwd_check(B, H, T, d, dv, C, g, dtype) != KATA_OK) return -1;
+  return kata::bwd_form(B * H, T, d, dv, C, g, dtype == KATA_BF16);
 }
 
 kata_status_t kata_bwd_chunked_ws(const void* q, const void* k, const void* v, const float* out,

@@ -23,6 +23,7 @@
 // then z[f] (n), fp32.
 #include <type_traits>
 
+#include "kata.h"
 #include "kata_common.hpp"
 #include "kata_internal.hpp"
 #include "kata_scan.hpp"
@@ -899,6 +900,12 @@ bool bwd_supported(int d, int dv, int C, int g) {
          (!bwd_mf_ok(d, dv, C) || bwd_grad_mf_smem(d, g, false) <= 160 * 1024);
 }
 
+int bwd_form(int BH, int T, int d, int dv, int C, int g, bool bf16_in) {
+  const bool bf = bf16_in && bwd_bf_ok(d, dv, C, g);
+  if (bf ? bwd_quad_ok(BH, T) : quad32_bwd_ok(BH, T, d, dv, C, g)) return KATA_BWD_QUADRATIC;
+  return bf && bwd_fused_scan(BH, d, dv, C, g, true) ? KATA_BWD_FUSED_STATES : KATA_BWD_STATES;
+}
+
 template <typename Tin>
 hipError_t launch_bwd(const void* q, const void* k, const void* v, const float* out,
                       const float* dout, const float* den, float* dq, float* dk, float* dv_out,
@@ -923,15 +930,15 @@ hipError_t launch_bwd(const void* q, const void* k, const void* v, const float* 
   // (the C ABI has checked that every tensor is 16-byte aligned)
   bool bf = false;
   if constexpr (std::is_same<Tin, bf16_t>::value) bf = bwd_bf_ok(d, dv, C, g);
-  if (bf && bwd_quad_ok(BH, T))
-    return launch_bwd_quad(q, k, v, out, dout, den, dq, dk, dv_out, BH, T, ws, st, ev);
-  if (!bf && quad32_bwd_ok(BH, T, d, dv, C, g))
-    return launch_quad32_bwd<Tin>(q, k, v, out, dout, den, dq, dk, dv_out, BH, T, d, dv, ws, st,
-                                  ev);
+  const int form = bwd_form(BH, T, d, dv, C, g, std::is_same<Tin, bf16_t>::value);
+  if (form == KATA_BWD_QUADRATIC)
+    return bf ? launch_bwd_quad(q, k, v, out, dout, den, dq, dk, dv_out, BH, T, ws, st, ev)
+              : launch_quad32_bwd<Tin>(q, k, v, out, dout, den, dq, dk, dv_out, BH, T, d, dv, ws,
+                                       st, ev);
   // bf16 path: from bwd_bf_fused_min_heads() heads on, each state launch also
   // scans (one pass, sequential over a head's chunks); with fewer heads the
   // chunk-parallel state launch and the record scan are faster
-  const bool fused = bf && bwd_fused_scan(BH, d, dv, C, g, true);
+  const bool fused = form == KATA_BWD_FUSED_STATES;
   hipError_t e = record(ev, 0, st);
   if (e != hipSuccess) return e;
   if (fused) {

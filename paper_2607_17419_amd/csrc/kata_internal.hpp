@@ -122,6 +122,9 @@ hipError_t launch_bwd_quad(const void* q, const void* k, const void* v, const fl
                            const float* dout, const float* den, float* dq, float* dk,
                            float* dv_out, int BH, int T, void* ws, hipStream_t st, hipEvent_t* ev);
 size_t bwd_workspace(int BH, int T, int d, int dv, int C, int g);
+// The form of a supported backward: KATA_BWD_STATES, _FUSED_STATES or _QUADRATIC of
+// kata.h.
+int bwd_form(int BH, int T, int d, int dv, int C, int g, bool bf16_in);
 // ev: null, or 7 events recorded before the first kernel and after each of the
 // six launches (forward states, prefix scan, coefficients, backward states,
 // suffix scan, gradients).  den: null, or the forward's denominators D_t

@@ -270,6 +270,42 @@ def test_bwd_fused_scan_host_logic():
     assert kata.bwd_fused_scan(8, 16, 4096, 64, 64, 64, 1, kata.KATA_BF16) == 1
 
 
+def test_forms_host_logic():
+    f, b = kata.fwd_form, kata.bwd_form
+    F32, BF = kata.KATA_F32, kata.KATA_BF16
+    # bf16 forward: quadratic up to a length, where the span is left to the library
+    assert f(8, 16, 4096, 64, 64, 64, 1, BF) == kata.FWD_QUADRATIC
+    assert f(8, 16, 4096, 64, 64, 64, 1, BF, span_chunks=16) == kata.FWD_STATES
+    assert f(1, 2, 6144, 64, 64, 64, 1, BF) == kata.FWD_QUADRATIC
+    assert f(1, 2, 6145, 64, 64, 64, 1, BF) == kata.FWD_STATES
+    assert f(1, 16, 5632, 64, 64, 64, 2, BF) == kata.FWD_QUADRATIC
+    assert f(1, 17, 5632, 64, 64, 64, 2, BF) == kata.FWD_STATES
+    assert f(1, 1, 8, 65, 64, 64, 1, BF) == f(1, 1, 8, 64, 64, 64, 3, BF) == -1
+    assert f(1, 1, 8, 64, 64, 64, 1, BF, span_chunks=-1) == f(1, 1, 8, 64, 64, 64, 1, 5) == -1
+    # fp32 forward: widths, heads and chunk size on both sides, whatever the span
+    assert f(1, 8, 1000, 64, 64, 64, 1, F32, span_chunks=3) == kata.FWD_QUADRATIC
+    assert f(1, 8, 62400, 64, 64, 64, 1, F32) == kata.FWD_QUADRATIC
+    assert f(1, 8, 62401, 64, 64, 64, 1, F32) == kata.FWD_STATES
+    assert f(1, 8, 16384, 64, 1, 64, 1, F32) == kata.FWD_STATES
+    assert f(1, 8, 1024, 4, 4, 64, 1, F32) == kata.FWD_QUADRATIC
+    assert f(8, 8, 4096, 4, 4, 64, 1, F32) == kata.FWD_STATES
+    assert f(8, 8, 4096, 4, 4, 1, 1, F32) == kata.FWD_QUADRATIC  # one state per token
+    assert f(1, 2, 300, 16, 16, 32, 2, F32) == kata.FWD_STATES   # feature blocks
+    # 65535 heads of 4200 tokens would be 2^32 threads and more
+    assert f(65535, 1, 4200, 64, 64, 64, 1, F32) == kata.FWD_STATES
+    # backward
+    assert b(8, 16, 4096, 64, 64, 64, 1, BF) == kata.BWD_QUADRATIC
+    assert b(1, 16, 8193, 64, 64, 64, 1, BF) == kata.BWD_FUSED_STATES
+    assert b(1, 7, 4097, 64, 64, 64, 1, BF) == kata.BWD_STATES
+    assert b(1, 2, 300, 64, 64, 32, 2, BF) == kata.BWD_STATES
+    assert b(1, 8, 8192, 64, 64, 64, 1, F32) == kata.BWD_QUADRATIC
+    assert b(1, 8, 8193, 64, 64, 64, 1, F32) == kata.BWD_STATES
+    assert b(1, 8, 1024, 8, 64, 64, 1, F32) == kata.BWD_QUADRATIC
+    assert b(1, 8, 4096, 8, 64, 64, 1, F32) == kata.BWD_STATES
+    assert b(1, 8, 100, 64, 65, 32, 1, F32) == kata.BWD_STATES   # wide values
+    assert b(1, 8, 100, 64, 64, 65, 1, F32) == -1
+
+
 def test_bwd_workspace_host_logic():
     L = kata.lib()
     # forward and backward records (n dv + n fp32 per chunk) plus (a_t, b_t)
