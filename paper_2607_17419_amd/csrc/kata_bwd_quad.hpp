@@ -357,12 +357,13 @@ __global__ __launch_bounds__(256) void bwd_quad_coef(const float* __restrict__ o
 
 }  // namespace
 
-// Quadratic time against the chunk states' linear one, measured (us, with the
-// denominators given): one head T4096 106 : 143, T8192 199 : 177; two heads
-// T8192 210 : 189; eight heads T8192 368 : 631, 64 heads T8192 2330 : 3313,
-// T10240 3703 : 4160, T12288 5258 : 5000.  With few heads a workgroup's walk
-// over T bounds the time, so they cross earlier; without the denominators one
-// more score pass is due and 64 heads cross at T10240 (4364 : 4366).
+// Quadratic time against the chunk states' linear one, measured at 1, 2, 5, 7, 8, 9, 15,
+// 16, 17, 33, 64, 100 and 250 heads (us, with the denominators given): one head T4096
+// 101 : 139, T6000 145 : 157, T8192 195 : 176; two heads T8192 199 : 182; eight heads T8192
+// 347 : 617; 17 heads 631 : 1059; 100 heads 4095 : 4761 (64 heads T10240 3703 : 4160,
+// T12288 5258 : 5000).  With few heads a workgroup's walk over T bounds the time, so they
+// cross earlier; without the denominators one more score pass is due: one head T4096
+// 145 : 147, 64 heads T8192 2781 : 3447.
 bool bwd_quad_ok(int BH, int T) { return T <= 4096 || (T <= 8192 && BH >= 8); }
 
 hipError_t launch_bwd_quad(const void* q, const void* k, const void* v, const float* out,

@@ -241,17 +241,18 @@ hipError_t run(const void* q, const void* k, const void* v, float* out, float* d
 
 }  // namespace
 
-// Quadratic time against the span pipeline's linear one, measured (us, this
-// form : spans of the default length): d = 64 two heads T2048 18 : 75, T6000 45 :
-// 76; 16 heads T1000 14 : 28, T4096 43 : 97, T6000 80 : 104; 128 heads T1000
-// 33 : 34, T2048 86 : 206, T4096 295 : 419, T6000 585 : 633, T8192 1005 : 860.
-// Two feature blocks: 16 heads T5000 64 : 80, T6000 83 : 84; 128 heads T3000
-// 181 : 222, T4096 311 : 303.  d = 32: 16 heads T4096 37 : 47, T5000 51 : 49; 128
-// heads T3000 141 : 151, T4096 237 : 202.
+// Quadratic time against the span pipeline's linear one, measured at 1, 2, 5, 16, 24,
+// 33, 64, 100, 128, 250 and 512 heads (us, this form : spans of the default length).
+// d = 64: 2 heads T2048 18 : 74, T6144 44 : 75; 16 heads T4096 43 : 86, T6144 83 : 92; 33
+// heads T6144 184 : 180; 64 heads 315 : 314; 128 heads T1000 31 : 30, T4096 288 : 395,
+// T6144 592 : 620; 250 heads T5000 858 : 960, T6144 1268 : 1191.  Two feature blocks: 16
+// heads T5632 77 : 75; 24 heads T3584 53 : 75, T5632 117 : 93; 250 heads T3584 439 : 524,
+// T5632 1097 : 812.  d = 32: 16 heads T4608 45 : 46; 24 heads T3072 32 : 45, T4608 63 :
+// 49; 512 heads T3072 517 : 525.
 bool quad_fwd_ok(int BH, int T, int d, int g) {
   if (d == 32) return T <= 3072 || (T <= 4608 && BH <= 16);
   if (g == 2) return T <= 3584 || (T <= 5632 && BH <= 16);
-  return T <= 6144;
+  return T <= (BH <= 128 ? 6144 : 5632);
 }
 
 hipError_t launch_quad_fwd(const void* q, const void* k, const void* v, float* out, float* den,

@@ -278,6 +278,8 @@ def test_forms_host_logic():
     assert f(8, 16, 4096, 64, 64, 64, 1, BF, span_chunks=16) == kata.FWD_STATES
     assert f(1, 2, 6144, 64, 64, 64, 1, BF) == kata.FWD_QUADRATIC
     assert f(1, 2, 6145, 64, 64, 64, 1, BF) == kata.FWD_STATES
+    assert f(8, 16, 6144, 64, 64, 64, 1, BF) == kata.FWD_QUADRATIC
+    assert f(129, 1, 6144, 64, 64, 64, 1, BF) == kata.FWD_STATES
     assert f(1, 16, 5632, 64, 64, 64, 2, BF) == kata.FWD_QUADRATIC
     assert f(1, 17, 5632, 64, 64, 64, 2, BF) == kata.FWD_STATES
     assert f(1, 1, 8, 65, 64, 64, 1, BF) == f(1, 1, 8, 64, 64, 64, 3, BF) == -1

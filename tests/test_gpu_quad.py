@@ -53,6 +53,7 @@ def test_one_and_two_waves_per_tile(kata, orc, B, H, T):
 
 @pytest.mark.parametrize("name,g,B,H,T", [("mid_bf16", 1, 1, 2, 6144), ("mid_bf16", 2, 1, 17, 3584),
                                           ("mid_bf16", 2, 1, 2, 5632),
+                                          ("mid_bf16", 1, 1, 129, 5632),
                                           ("recall_bf16", 1, 1, 17, 3072),
                                           ("recall_bf16", 1, 1, 2, 4608)])
 def test_default_forward_either_side_of_the_rule(kata, name, g, B, H, T):
