@@ -731,7 +731,9 @@ hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const
   // Measured (us, wide : 256 threads; d = 64, the same state each step / four in
   // turn): 64 heads (34 MB) 16 / 18 : 29 / 29 cached; 128 heads 29 / 30 : 33 / 33
   // and 256 heads (136 MB) 52 / 52 : 53 / 54 past the caches, 1024 heads 203 : 197;
-  // d = 32 (135 KB per head) 1024 heads 50 : 58, 4096 heads 186 : 207.
+  // d = 32 (135 KB per head) 1024 heads 50 : 58, 4096 heads 186 : 207.  Past the caches
+  // heads of 2.1 MB (d = 64 dv = 256) take 75 : 67 (24 of them) to 95 : 86 (64), in the
+  // caches 43 : 58 (16); heads of 1.2 MB (48, 256) 51 : 54 (48) and 56 : 58 (64).
   const int n = g * ((d / g) * (d / g + 1) / 2);
   const size_t head = static_cast<size_t>(n) * dv * sizeof(float), state = head * BH;
   const bool pow2 = dv >= 4 && dv <= 256 && (dv & (dv - 1)) == 0;
@@ -746,7 +748,8 @@ hipError_t launch_decode(float* S, float* z, const void* q, const void* k, const
   // A launch holds fewer than 2^32 threads: 256 per head serve four times as many heads.
   const bool fits = static_cast<long long>(BH) * kWideThreads < (1LL << 32);
   if (pow2 && fits && (few || head >= (18u << 10)) &&
-      (state <= (140u << 20) || head <= (160u << 10))) {
+      (state <= (48u << 20) || (state <= (140u << 20) && head <= (1300u << 10)) ||
+       head <= (160u << 10))) {
     const unsigned m = d / g, inv_m = ((1u << 20) + m - 1) / m;  // exact quotients below 64 m
     auto go = [&](auto nt) {
       decode_wide_f32<Tin, decltype(nt)::value><<<BH, kWideThreads, 0, st>>>(

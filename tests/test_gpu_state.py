@@ -84,6 +84,7 @@ def test_state_overflow_matches_fp32(kata):
 @pytest.mark.parametrize("B,H,d,dv,g", [
     (1, 1, 64, 64, 1), (1, 3, 1, 4, 1), (2, 2, 33, 32, 1), (1, 5, 24, 128, 3), (1, 2, 64, 256, 2),
     (3, 1, 40, 8, 5), (1, 2, 48, 24, 1), (1, 2, 7, 5, 1), (6, 16, 64, 64, 1), (18, 16, 64, 64, 1),
+    (24, 1, 64, 256, 1),  # large heads past the caches
     # small heads: 512 and more than 512 of them, 1280 and more for eight columns
     (64, 8, 8, 16, 1), (513, 1, 8, 16, 2), (160, 8, 16, 8, 1), (1281, 1, 16, 8, 1)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
