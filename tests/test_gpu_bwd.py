@@ -7,9 +7,11 @@ scale (max |ref|, at least 1); bf16 inputs, the relative l2 error of each
 gradient tensor per head <= 2e-2.  Rows with a small denominator D_t have
 large gradients (a_t = dout_t / D_t), hence the scale-relative forms.
 
-Two gradient kernels serve bf16 inputs.  For d = dv = C = 64 and one feature
-block the products run on the bf16 matrix cores: the prefix and suffix states
-and the in-chunk score products are rounded to bf16 once (8 significant bits,
+Two kinds of gradient kernels serve bf16 inputs.  For d = dv = C = 64 and one
+feature block the products run on the bf16 matrix cores, quadratically over
+short sequences and through chunk states over longer ones (kata.bwd_form
+tells): the score products, and the prefix and suffix states where there are
+any, are rounded to bf16 once (8 significant bits,
 unit roundoff u = 2^-8), and every product of the gradients carries at most
 two rounded factors, so each term is off by at most 2u = 2^-7 relative.  Fed
 the exact forward output, that path is held to the bf16 bound 2e-2 (2.5 x
@@ -150,16 +152,18 @@ def test_bwd_ragged_m1(kata, orc, T):
 @pytest.mark.parametrize("B,H,T", [(2, 16, 333), (3, 6, 130), (2, 8, 200), (1, 40, 64),
                                    (16, 1, 37)])
 def test_bwd_fused_state_scan(kata, orc, B, H, T):
-    # From 16 heads on, the bf16 path computes each record stream (prefix of the
-    # forward states, suffix of the backward states) in one launch that walks a
-    # head's chunks in order; with fewer heads it runs the chunk-parallel state
-    # launch and a scan.  B x H = 32, 18 (not a multiple of the 8 heads a
-    # workgroup row spans), 16 (the smallest fused count), 40 with a single
-    # chunk and 16 batches of one head with one partial chunk; against the
-    # oracle, and
-    # against the same heads run one at a time (the other path).
+    # From 16 heads on, the chunk-state backward computes each record stream
+    # (prefix of the forward states, suffix of the backward states) in one launch
+    # that walks a head's chunks in order; with fewer heads it runs the
+    # chunk-parallel state launch and a scan.  Sequences as short as the first five
+    # are evaluated quadratically whatever the head count: B x H = 32, 18 (not a
+    # multiple of eight), 16, 40 with a single chunk and 16 batches of one head with
+    # one partial chunk; test_bwd_fused_state_scan_past_quadratic takes the fused
+    # form.  Against the oracle, and against the same heads run one at a time.
     import torch
-    log(f"case bwd fused state+scan bf16 B{B} H{H} T{T} d64 dv64 C64")
+    form = kata.bwd_form(B, H, T, 64, 64, 64, 1, kata.KATA_BF16)
+    assert form == kata.BWD_QUADRATIC
+    log(f"case bwd of many heads, short sequences, bf16 B{B} H{H} T{T} d64 dv64 C64")
     inp = workloads.make_inputs("mid_bf16", B=B, H=H, T=T)
     dout = _dout(inp["v"].shape, 41 + H)
     ref = orc.bwd_mg(inp["q"], inp["k"], inp["v"], dout, 1)
@@ -177,18 +181,73 @@ def test_bwd_fused_state_scan(kata, orc, B, H, T):
             a = a.cpu().numpy()[0, 0].astype(np.float64)
             g_ = g_[b, h].astype(np.float64)
             rel = np.linalg.norm(a - g_) / max(np.linalg.norm(g_), 1e-30)
-            log(f"  head ({b}, {h}) {name}: fused vs per-head rel l2 {rel:.3e}")
+            log(f"  head ({b}, {h}) {name}: together vs per-head rel l2 {rel:.3e}")
             assert rel <= BF16_GRAD_REL, (b, h, name)
+
+
+def _check_heads(kata, orc, inp, dout, got, heads, what):
+    """The gradients of the given (batch, head) pairs against the oracle."""
+    for b, h in heads:
+        sel = lambda x: x[b, h][None, None]
+        ref = orc.bwd_mg(sel(inp["q"]), sel(inp["k"]), sel(inp["v"]), sel(dout), 1)
+        _check_rel(tuple(sel(g_.cpu().numpy()) for g_ in got), ref, f"{what} head {b}, {h}",
+                   tol=BF16_GRAD_REL)
+
+
+@pytest.mark.parametrize("B,H,T", [(1, 16, 8192 + 37), (2, 9, 8192 + 64)])
+def test_bwd_fused_state_scan_past_quadratic(kata, orc, B, H, T):
+    # 16 heads (the smallest fused count) with a partial last chunk, and 18 (not a
+    # multiple of the 8 heads a workgroup row spans), past the length of the
+    # quadratic form: the exact forward output and denominators on the first and
+    # the last head, with and without the saved denominators
+    import torch
+    log(f"case bwd fused state+scan bf16 B{B} H{H} T{T} d64 dv64 C64")
+    assert kata.bwd_form(B, H, T, 64, 64, 64, 1, kata.KATA_BF16) == kata.BWD_FUSED_STATES
+    inp = workloads.make_inputs("mid_bf16", B=B, H=H, T=T)
+    q, k, v = (to_device(inp[n], "bf16") for n in ("q_dev", "k_dev", "v_dev"))
+    out, den = kata.fwd_chunked_train(q, k, v, 64)
+    heads = ((0, 0), (B - 1, H - 1))
+    for b, h in heads:
+        one = tuple(inp[n][b, h][None, None] for n in ("q", "k", "v"))
+        out[b, h] = torch.from_numpy(orc.fwd(*one)[0, 0].astype(np.float32)).cuda()
+        den[b, h] = torch.from_numpy(orc.den(*one[:2])[0, 0].astype(np.float32)).cuda()
+    dout = _dout(inp["v"].shape, 59 + H)
+    d_out = torch.from_numpy(dout).to(q.device)
+    for what, d_ in (("own den", None), ("saved den", den)):
+        got = kata.bwd_chunked(q, k, v, out, d_out, 64, 1, den=d_)
+        torch.cuda.synchronize()
+        _check_heads(kata, orc, inp, dout, got, heads, what)
+
+
+@pytest.mark.parametrize("H,T", [(1, 4100), (2, 4096 + 64 + 1)])
+def test_bwd_chunk_parallel_past_quadratic(kata, orc, H, T):
+    # few heads past the length of the quadratic form: the chunk-parallel state
+    # launch and the record scan, against the oracle
+    import torch
+    log(f"case bwd chunk-parallel states bf16 B1 H{H} T{T} d64 dv64 C64")
+    assert kata.bwd_form(1, H, T, 64, 64, 64, 1, kata.KATA_BF16) == kata.BWD_STATES
+    inp = workloads.make_inputs("mid_bf16", B=1, H=H, T=T)
+    q, k, v = (to_device(inp[n], "bf16") for n in ("q_dev", "k_dev", "v_dev"))
+    o_ref = orc.fwd(inp["q"], inp["k"], inp["v"]).astype(np.float32)
+    den = torch.from_numpy(orc.den(inp["q"], inp["k"]).astype(np.float32)).cuda()
+    out = torch.from_numpy(np.ascontiguousarray(o_ref)).cuda()
+    dout = _dout(inp["v"].shape, 61 + H)
+    for what, d_ in (("own den", None), ("saved den", den)):
+        got = kata.bwd_chunked(q, k, v, out, torch.from_numpy(dout).cuda(), 64, 1, den=d_)
+        torch.cuda.synchronize()
+        _check_heads(kata, orc, inp, dout, got, ((0, 0), (0, H - 1)), what)
 
 
 def test_bwd_bench_configuration_sampled_heads(kata, orc):
     # the training step's own shape (the mid workload, B8 H16 T4096, 128 heads:
-    # the fused state+scan path) against the oracle on three heads; those
-    # heads get the exact forward output, so the per-row bound applies
+    # short enough for the quadratic form; its chunk states would be fused with
+    # their scan) against the oracle on three heads; those heads get the exact
+    # forward output, so the per-row bound applies
     import torch
     w = workloads.WORKLOADS["mid_bf16"]
     log(f"case bwd bench configuration B{w.B} H{w.H} T{w.T} d64 C64, heads 0, 77, 127")
     assert kata.bwd_fused_scan(w.B, w.H, w.T, 64, 64, 64, 1, kata.KATA_BF16) == 1
+    assert kata.bwd_form(w.B, w.H, w.T, 64, 64, 64, 1, kata.KATA_BF16) == kata.BWD_QUADRATIC
     inp = workloads.make_inputs("mid_bf16")
     q, k, v = (to_device(inp[n], "bf16") for n in ("q_dev", "k_dev", "v_dev"))
     out = kata.fwd_chunked(q, k, v, 64)
@@ -378,12 +437,12 @@ def test_bwd_full_length_two_heads(kata, orc):
 # library's own forward output, to the per-head bound.
 # ---------------------------------------------------------------------------
 @pytest.mark.parametrize("B,H,T", [(1, 16, 1100), (1, 2, 700), (2, 3, 257), (1, 16, 4096),
-                                   (1, 2, 1), (1, 3, 63)])
+                                   (1, 2, 1), (1, 3, 63), (1, 16, 8200), (1, 2, 4200)])
 def test_bwd_with_saved_denominators(kata, orc, B, H, T):
     import torch
-    fused = kata.bwd_fused_scan(B, H, T, 64, 64, 64, 1, kata.KATA_BF16)
-    log(f"case train forward + backward with saved D_t: B{B} H{H} T{T} d64 C64 "
-        f"(state and scan fused: {fused})")
+    form = kata.bwd_form(B, H, T, 64, 64, 64, 1, kata.KATA_BF16)
+    log(f"case train forward + backward with saved D_t: B{B} H{H} T{T} d64 C64, form {form}")
+    assert form == {8200: kata.BWD_FUSED_STATES, 4200: kata.BWD_STATES}.get(T, kata.BWD_QUADRATIC)
     inp = workloads.make_inputs("mid_bf16", B=B, H=H, T=T)
     q, k, v = (to_device(inp[n], "bf16") for n in ("q_dev", "k_dev", "v_dev"))
     out, den = kata.fwd_chunked_train(q, k, v, 64)

@@ -59,23 +59,30 @@ def _capture(fn):
     return g
 
 
-def test_forward_workspace_graph(kata):
+@pytest.mark.parametrize("span", [16, 0])
+def test_forward_workspace_graph(kata, span):
     import torch
     B, H, T, C = 1, 4, 3000, 64
-    log(f"case graph: kata_fwd_chunked_ws B{B} H{H} T{T} d64 C{C} (three spans, ragged)")
+    log(f"case graph: kata_fwd_chunked_ws B{B} H{H} T{T} d64 C{C} "
+        f"({'three spans, ragged' if span else 'quadratic'})")
+    assert kata.fwd_form(B, H, T, 64, 64, C, 1, kata.KATA_BF16, span) == (
+        kata.FWD_STATES if span else kata.FWD_QUADRATIC)
     q, k, v = _dev3(workloads.make_inputs("mid_bf16", B=B, H=H, T=T))
     ws = torch.empty(kata.workspace_bytes(B, H, T, 64, 64, C, kata.KATA_BF16), dtype=torch.uint8,
                      device="cuda:0")
-    ref = kata.fwd_chunked(q, k, v, C, workspace=ws).cpu().numpy()
+    ref = kata.fwd_chunked(q, k, v, C, span_chunks=span, workspace=ws).cpu().numpy()
     out = torch.empty((B, H, T, 64), dtype=torch.float32, device="cuda:0")
-    g = _capture(lambda: kata.fwd_chunked(q, k, v, C, out=out, workspace=ws))
+    g = _capture(lambda: kata.fwd_chunked(q, k, v, C, span_chunks=span, out=out, workspace=ws))
     _replay_and_check(g, [out], [ref], "forward (workspace)")
 
 
-def test_forward_noalloc_graph(kata):
+@pytest.mark.parametrize("T", [6200, 2100])
+def test_forward_noalloc_graph(kata, T):
     import torch
-    B, H, T, C = 2, 2, 2100, 64
-    log(f"case graph: kata_fwd_chunked_noalloc B{B} H{H} T{T} d64 C{C}")
+    B, H, C = 2, 2, 64
+    form = kata.fwd_form(B, H, T, 64, 64, C, 1, kata.KATA_BF16)
+    log(f"case graph: kata_fwd_chunked_noalloc B{B} H{H} T{T} d64 C{C}, form {form}")
+    assert form == (kata.FWD_STATES if T == 6200 else kata.FWD_QUADRATIC)
     q, k, v = _dev3(workloads.make_inputs("mid_bf16", B=B, H=H, T=T))
     ref = kata.fwd_chunked_noalloc(q, k, v, C).cpu().numpy()
     out = torch.empty((B, H, T, 64), dtype=torch.float32, device="cuda:0")
@@ -96,12 +103,15 @@ def test_quadratic_graph(kata):
     _replay_and_check(g, [out], [ref], "quadratic form")
 
 
-@pytest.mark.parametrize("H,T", [(16, 1100), (2, 700)])
+# quadratic, and past its length the states fused with their scan and apart from it
+@pytest.mark.parametrize("H,T", [(16, 1100), (2, 700), (16, 8200), (2, 4200)])
 def test_backward_graph(kata, H, T):
     import torch
     B, C = 1, 64
-    fused = kata.bwd_fused_scan(B, H, T, 64, 64, C, 1, kata.KATA_BF16)
-    log(f"case graph: kata_bwd_chunked_ws B{B} H{H} T{T} d64 C{C} (state and scan fused: {fused})")
+    form = kata.bwd_form(B, H, T, 64, 64, C, 1, kata.KATA_BF16)
+    log(f"case graph: kata_bwd_chunked_ws B{B} H{H} T{T} d64 C{C}, form {form}")
+    assert form == {1100: kata.BWD_QUADRATIC, 700: kata.BWD_QUADRATIC,
+                    8200: kata.BWD_FUSED_STATES, 4200: kata.BWD_STATES}[T]
     q, k, v = _dev3(workloads.make_inputs("mid_bf16", B=B, H=H, T=T))
     out = kata.fwd_chunked(q, k, v, C)
     gen = torch.Generator(device="cuda:0")
@@ -144,11 +154,13 @@ def test_decode_step_graph(kata):
         assert np.array_equal(z_g.cpu().numpy(), rz), f"decode replay {r}: z differs"
 
 
-def test_training_pair_graph(kata):
+@pytest.mark.parametrize("T", [1100, 8200])
+def test_training_pair_graph(kata, T):
     # the forward that saves the denominators and the backward that takes
-    # them, captured together as one training step
+    # them, captured together as one training step: both quadratic, and through
+    # span states and fused chunk states
     import torch
-    B, H, T, C = 1, 16, 1100, 64
+    B, H, C = 1, 16, 64
     log(f"case graph: kata_fwd_chunked_train_ws + kata_bwd_chunked_ex B{B} H{H} T{T} d64 C{C}")
     q, k, v = _dev3(workloads.make_inputs("mid_bf16", B=B, H=H, T=T))
     gen = torch.Generator(device="cuda:0")
@@ -195,15 +207,17 @@ def test_linear_features_graph(kata, feature):
     _replay_and_check(g, [out], [ref], f"linear feature {feature}")
 
 
-def test_mg_graph(kata):
+@pytest.mark.parametrize("span", [16, 0])
+def test_mg_graph(kata, span):
     import torch
     B, H, T, C = 1, 4, 2500, 64
-    log(f"case graph: kata_mg_fwd_chunked_ws g2 B{B} H{H} T{T} d64 C{C}")
+    log(f"case graph: kata_mg_fwd_chunked_ws g2 B{B} H{H} T{T} d64 C{C} span_chunks={span}")
     q, k, v = _dev3(workloads.make_inputs("mid_bf16", B=B, H=H, T=T))
     ws = torch.empty(max(256, int(kata.lib().kata_mg_fwd_workspace_bytes(B, H, T, 64, 64, C, 2,
                                                                           kata.KATA_BF16, 0))),
                      dtype=torch.uint8, device="cuda:0")
-    ref = kata.mg_fwd_chunked(q, k, v, C, 2, workspace=ws).cpu().numpy()
+    ref = kata.mg_fwd_chunked(q, k, v, C, 2, span_chunks=span, workspace=ws).cpu().numpy()
     out = torch.empty((B, H, T, 64), dtype=torch.float32, device="cuda:0")
-    g = _capture(lambda: kata.mg_fwd_chunked(q, k, v, C, 2, out=out, workspace=ws))
+    g = _capture(lambda: kata.mg_fwd_chunked(q, k, v, C, 2, span_chunks=span, out=out,
+                                             workspace=ws))
     _replay_and_check(g, [out], [ref], "KATA-M2")

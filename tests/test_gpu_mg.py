@@ -36,15 +36,19 @@ def _run(kata, inp, dtype, C, g, span=0):
 
 
 @pytest.mark.parametrize("T", [1, 2, 33, 257, 1025, 2100])
-def test_m2_ragged(kata, orc, T):
-    log(f"case M2 (bf16 MFMA) ragged T={T} B1 H2 d64 g2 C64")
+@pytest.mark.parametrize("span", [16, 0])
+def test_m2_ragged(kata, orc, T, span):
+    # through states with a span given, else in the quadratic form
+    log(f"case M2 (bf16 MFMA) ragged T={T} B1 H2 d64 g2 C64 span_chunks={span}")
+    assert kata.fwd_form(1, 2, T, 64, 64, 64, 2, kata.KATA_BF16, span) == (
+        kata.FWD_STATES if span else kata.FWD_QUADRATIC)
     inp = workloads.make_inputs("mid_bf16", B=1, H=2, T=T)
-    got = _run(kata, inp, "bf16", 64, 2)
+    got = _run(kata, inp, "bf16", 64, 2, span)
     ref = orc.fwd_mg(inp["q"], inp["k"], inp["v"], 2)
     assert_bf16_close(got, ref, f"M2 T {T}")
 
 
-@pytest.mark.parametrize("C,span", [(64, 1), (64, 4), (32, 16), (128, 8), (256, 0)])
+@pytest.mark.parametrize("C,span", [(64, 1), (64, 4), (32, 16), (128, 8), (256, 0), (256, 4)])
 def test_m2_spans_and_chunks(kata, orc, C, span):
     T = 2500
     log(f"case M2 C={C} span={span} B1 H2 T{T}")
@@ -106,13 +110,14 @@ def test_mg_g1_is_m1(kata):
     assert torch.equal(a, b)
 
 
-def test_m2_zero_query_rows(kata, orc):
-    log("case M2 zero query rows (D_t = 0 -> 0)")
+@pytest.mark.parametrize("span", [11, 0])
+def test_m2_zero_query_rows(kata, orc, span):
+    log(f"case M2 zero query rows (D_t = 0 -> 0), span_chunks={span}")
     inp = workloads.make_inputs("mid_bf16", B=1, H=1, T=700)
     for key in ("q_dev", "q"):
         inp[key] = inp[key].copy()
         inp[key][0, 0, [0, 5, 64, 640]] = 0
-    got = _run(kata, inp, "bf16", 64, 2)
+    got = _run(kata, inp, "bf16", 64, 2, span)
     assert np.all(got[0, 0, [0, 5, 64, 640]] == 0.0)
     ref = orc.fwd_mg(inp["q"], inp["k"], inp["v"], 2)
     assert_bf16_close(got, ref, "M2 zero rows")

@@ -29,11 +29,21 @@ def _inputs(name, **kw):
     return workloads.make_inputs(name, **kw)
 
 
-def _run_fwd(kata, inp, dtype, C, span=0):
+# The bf16 forward of a short sequence runs in the quadratic form where the span is
+# left to the library, and through span states where it is given: "default" and
+# "spans" (the span that longer sequences get) take one each.
+FORMS = pytest.mark.parametrize("form", ["spans", "default"])
+
+
+def _run_fwd(kata, inp, dtype, C, span=0, form="default"):
     import torch
     q = to_device(inp["q_dev"], dtype)
     k = to_device(inp["k_dev"], dtype)
     v = to_device(inp["v_dev"], dtype)
+    if form == "spans":
+        B, H, T, d = q.shape
+        span = kata.default_span(B, H, T, d, v.shape[3], C, kata.KATA_BF16)
+        assert kata.fwd_form(B, H, T, d, v.shape[3], C, 1, kata.KATA_BF16, span) == kata.FWD_STATES
     out = kata.fwd_chunked(q, k, v, C, span_chunks=span)
     torch.cuda.synchronize()
     return out.cpu().numpy()
@@ -84,10 +94,11 @@ def test_bf16_on_fp32_path(kata, orc):
 # bf16 MFMA path
 # ---------------------------------------------------------------------------
 
-def test_mid_bf16_two_heads_full(kata, orc):
-    log("case mid_bf16 B1 H2 T4096 (all rows)")
+@FORMS
+def test_mid_bf16_two_heads_full(kata, orc, form):
+    log(f"case mid_bf16 B1 H2 T4096 (all rows), {form}")
     inp = _inputs("mid_bf16", B=1, H=2)
-    got = _run_fwd(kata, inp, "bf16", 64)
+    got = _run_fwd(kata, inp, "bf16", 64, form=form)
     ref = orc.fwd(inp["q"], inp["k"], inp["v"])
     assert_bf16_close(got, ref, "mid_bf16 B1 H2")
 
@@ -105,21 +116,23 @@ def test_span_modes_agree(kata, orc, span):
     assert_bf16_close(got, ref, f"span {span}")
 
 
+@FORMS
 @pytest.mark.parametrize("C", [32, 64, 128, 256])
-def test_chunk_size_independent(kata, orc, C):
+def test_chunk_size_independent(kata, orc, C, form):
     T = 1500
-    log(f"case C={C} B1 H1 T{T} d64")
+    log(f"case C={C} B1 H1 T{T} d64, {form}")
     inp = _inputs("mid_bf16", B=1, H=1, T=T)
-    got = _run_fwd(kata, inp, "bf16", C)
+    got = _run_fwd(kata, inp, "bf16", C, form=form)
     ref = orc.fwd(inp["q"], inp["k"], inp["v"])
     assert_bf16_close(got, ref, f"C {C}")
 
 
+@FORMS
 @pytest.mark.parametrize("T", [1, 2, 31, 33, 63, 64, 65, 257, 1023, 1025])
-def test_ragged_lengths(kata, orc, T):
-    log(f"case ragged T={T} d64 C64")
+def test_ragged_lengths(kata, orc, T, form):
+    log(f"case ragged T={T} d64 C64, {form}")
     inp = _inputs("mid_bf16", B=1, H=2, T=T)
-    got = _run_fwd(kata, inp, "bf16", 64)
+    got = _run_fwd(kata, inp, "bf16", 64, form=form)
     ref = orc.fwd(inp["q"], inp["k"], inp["v"])
     assert_bf16_close(got, ref, f"T {T}")
 
@@ -134,34 +147,37 @@ def test_recall_d32(kata, orc, span):
     assert_bf16_close(got, ref, f"recall d32 span {span}")
 
 
-def test_zero_query_row(kata, orc):
-    log("case zero query rows (D_t = 0 -> 0)")
+@FORMS
+def test_zero_query_row(kata, orc, form):
+    log(f"case zero query rows (D_t = 0 -> 0), {form}")
     inp = _inputs("mid_bf16", B=1, H=1, T=700)
     for key in ("q_dev", "q"):
         inp[key] = inp[key].copy()
         inp[key][0, 0, [0, 5, 64, 640]] = 0
-    got = _run_fwd(kata, inp, "bf16", 64)
+    got = _run_fwd(kata, inp, "bf16", 64, form=form)
     assert np.all(got[0, 0, [0, 5, 64, 640]] == 0.0)
     ref = orc.fwd(inp["q"], inp["k"], inp["v"])
     assert_bf16_close(got, ref, "zero rows")
 
 
-def test_deterministic_and_metamorphic(kata):
+@FORMS
+def test_deterministic_and_metamorphic(kata, form):
     # No atomics: bitwise run-to-run identical.  q -> 2q scales every product
     # and sum by a power of two, so the output is bitwise unchanged.  k -> -k
     # leaves phi(k) and the squared scores unchanged in exact arithmetic, but
     # the matrix cores need not round a negated sum to the negated result, so
     # that one is held to a tight tolerance instead.
     import torch
-    log("case determinism + sign/scale invariance, B1 H2 T2100")
+    log(f"case determinism + sign/scale invariance, B1 H2 T2100, {form}")
+    span = 16 if form == "spans" else 0
     inp = _inputs("mid_bf16", B=1, H=2, T=2100)
     q = to_device(inp["q_dev"], "bf16")
     k = to_device(inp["k_dev"], "bf16")
     v = to_device(inp["v_dev"], "bf16")
-    a = kata.fwd_chunked(q, k, v, 64)
-    b = kata.fwd_chunked(q, k, v, 64)
-    c = kata.fwd_chunked(q, -k, v, 64)
-    e = kata.fwd_chunked(q * 2, k, v, 64)
+    a = kata.fwd_chunked(q, k, v, 64, span_chunks=span)
+    b = kata.fwd_chunked(q, k, v, 64, span_chunks=span)
+    c = kata.fwd_chunked(q, -k, v, 64, span_chunks=span)
+    e = kata.fwd_chunked(q * 2, k, v, 64, span_chunks=span)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
     assert torch.equal(a, e)
@@ -170,10 +186,13 @@ def test_deterministic_and_metamorphic(kata):
     assert diff < 1e-4
 
 
-def test_library_allocated_workspace(kata):
+@pytest.mark.parametrize("T", [1200, 6200])
+def test_library_allocated_workspace(kata, T):
     import torch
-    log("case kata_fwd_chunked (stream-ordered workspace) vs caller workspace")
-    inp = _inputs("mid_bf16", B=1, H=2, T=1200)
+    log(f"case kata_fwd_chunked (stream-ordered workspace) vs caller workspace, T{T}")
+    form = kata.fwd_form(1, 2, T, 64, 64, 64, 1, kata.KATA_BF16)
+    assert form == (kata.FWD_QUADRATIC if T == 1200 else kata.FWD_STATES)
+    inp = _inputs("mid_bf16", B=1, H=2, T=T)
     q = to_device(inp["q_dev"], "bf16")
     k = to_device(inp["k_dev"], "bf16")
     v = to_device(inp["v_dev"], "bf16")
@@ -225,12 +244,13 @@ def test_allocation_failure_then_success(kata):
 # ---------------------------------------------------------------------------
 
 # (the long workload's measurement row set is in test_gpu_scan_blocks.py)
-@pytest.mark.parametrize("name", ["mid_bf16", "recall_bf16"])
-def test_full_size_sampled(kata, orc, name):
+@pytest.mark.parametrize("name,form", [("mid_bf16", "spans"), ("mid_bf16", "default"),
+                                       ("recall_bf16", "default")])
+def test_full_size_sampled(kata, orc, name, form):
     w = workloads.WORKLOADS[name]
-    log(f"case full-size {name}: {w.note}")
+    log(f"case full-size {name}: {w.note}, {form}")
     inp = _inputs(name)
-    got = _run_fwd(kata, inp, "bf16", w.C)
+    got = _run_fwd(kata, inp, "bf16", w.C, form=form)
     assert np.all(np.isfinite(got))
     bh, tt = sample_rows(w.B, w.H, w.T, w.seed, n_random=4096, head_rows=1024, tail_rows=256)
     ref = orc.fwd_rows(inp["q"], inp["k"], inp["v"], bh, tt)
@@ -310,31 +330,34 @@ def test_decode_full_size_sampled(kata, orc):
 
 
 # ---------------------------------------------------------------------------
-# input magnitudes: the MFMA path's state products are fp16 with per-span
-# power-of-two scales; every case must match the oracle at the same bar
+# input magnitudes: the span states' products are fp16 with per-span power-of-two
+# scales, the quadratic form's weights bf16; every case must match the oracle at
+# the same bar
 # ---------------------------------------------------------------------------
 
+@FORMS
 @pytest.mark.parametrize("ks,vs", [(300.0, 1.0), (2.0 ** -10, 1.0), (1.0, 3.0e4), (1.0, 1e-6),
                                    (2.0 ** -40, 2.0 ** 20), (50.0, 200.0), (4.0, 50.0)])
-def test_input_magnitudes(kata, orc, ks, vs):
-    log(f"case magnitudes k x {ks:g}, v x {vs:g}: B1 H2 T2500 d64 C64")
+def test_input_magnitudes(kata, orc, ks, vs, form):
+    log(f"case magnitudes k x {ks:g}, v x {vs:g}: B1 H2 T2500 d64 C64, {form}")
     rng = np.random.default_rng(71)
     q, k, v = workloads.gaussian_qkv(rng, 1, 2, 2500, 64, 64)
     (qv, kv, vv), (qd, kd, vd) = workloads._finish([q, k * np.float32(ks), v * np.float32(vs)],
                                                    "bf16")
-    got = _run_fwd(kata, dict(q_dev=qd, k_dev=kd, v_dev=vd), "bf16", 64)
+    got = _run_fwd(kata, dict(q_dev=qd, k_dev=kd, v_dev=vd), "bf16", 64, form=form)
     assert_bf16_close(got, orc.fwd(qv, kv, vv), f"k x {ks:g}, v x {vs:g}")
 
 
-def test_later_block_outgrows_first(kata, orc):
+@FORMS
+def test_later_block_outgrows_first(kata, orc, form):
     # the first 128 keys of every span are unit vectors, later keys are 2000x
-    # larger (their fp16 feature products overflow without a scale): the
-    # span is redone with its exact scales
-    log("case later keys 2000x the first block's: B1 H2 T3000 d64 C64")
+    # larger (their fp16 feature products overflow without a scale): with span
+    # states, the span is redone with its exact scales
+    log(f"case later keys 2000x the first block's: B1 H2 T3000 d64 C64, {form}")
     rng = np.random.default_rng(72)
     q, k, v = workloads.gaussian_qkv(rng, 1, 2, 3000, 64, 64)
     big = (np.arange(3000) % 1024) >= 128
     k = k * np.where(big, np.float32(2000.0), np.float32(1.0))[None, None, :, None]
     (qv, kv, vv), (qd, kd, vd) = workloads._finish([q, k, v], "bf16")
-    got = _run_fwd(kata, dict(q_dev=qd, k_dev=kd, v_dev=vd), "bf16", 64)
+    got = _run_fwd(kata, dict(q_dev=qd, k_dev=kd, v_dev=vd), "bf16", 64, form=form)
     assert_bf16_close(got, orc.fwd(qv, kv, vv), "later keys 2000x")

@@ -63,17 +63,17 @@ def test_quadratic_zero_query_rows(kata, orc):
 
 def test_quadratic_matches_chunked(kata):
     import torch
-    log("case quadratic vs chunked B2 H4 T4096 d64")
+    log("case quadratic vs span states B2 H4 T4096 d64")
     inp = workloads.make_inputs("mid_bf16", B=2, H=4, T=4096)
     q = to_device(inp["q_dev"], "bf16")
     k = to_device(inp["k_dev"], "bf16")
     v = to_device(inp["v_dev"], "bf16")
     a = kata.fwd_quadratic(q, k, v)
-    b = kata.fwd_chunked(q, k, v, 64)
+    b = kata.fwd_chunked(q, k, v, 64, span_chunks=16)  # with no span given it is quadratic too
     torch.cuda.synchronize()
     a, b = a.cpu().numpy(), b.cpu().numpy()
     rel = np.linalg.norm(a - b, axis=-1) / np.linalg.norm(b, axis=-1)
-    log(f"  quadratic vs chunked: max row rel diff {rel.max():.3e}")
+    log(f"  quadratic vs span states: max row rel diff {rel.max():.3e}")
     assert rel.max() <= 2e-2
 
 

@@ -99,9 +99,12 @@ def test_m2_span1_past_128_records(kata, orc):
     assert_bf16_close(got, ref, "M2 span 1, 130 records")
 
 
-@pytest.mark.parametrize("T,C", [(300, 2), (1000, 3), (600, 1)])
+# up to T = 4096 the quadratic form serves these calls (no chunks), past it the scan
+@pytest.mark.parametrize("T,C", [(300, 2), (1000, 3), (600, 1), (4130, 32), (4200, 3)])
 def test_fp32_path_past_128_chunks(kata, orc, T, C):
-    log(f"case fp32 path d16 dv16 B1 H2 T{T} C{C} ({-(-T // C)} chunks per head)")
+    form = kata.fwd_form(1, 2, T, 16, 16, C, 1, kata.KATA_F32)
+    log(f"case fp32 path d16 dv16 B1 H2 T{T} C{C} ({-(-T // C)} chunks per head), form {form}")
+    assert form == (kata.FWD_STATES if T > 4096 else kata.FWD_QUADRATIC)
     rng = np.random.default_rng(T + C)
     q, k, v = workloads.gaussian_qkv(rng, 1, 2, T, 16, 16)
     got = _run(kata, dict(q_dev=q, k_dev=k, v_dev=v), "f32", C)

@@ -32,9 +32,12 @@ def _dev3(inp, dtype):
 def test_noalloc_matches_allocating_entry_point(kata, orc):
     import torch
     cases = [("mid_bf16", dict(B=2, H=3, T=5000), "bf16", 64),
-             ("mid_bf16", dict(B=1, H=2, T=777), "bf16", 64)]
+             ("mid_bf16", dict(B=1, H=2, T=777), "bf16", 64),
+             ("mid_bf16", dict(B=1, H=3, T=6200), "bf16", 64)]
     for name, shape, dtype, C in cases:
-        log(f"case noalloc vs kata_fwd_chunked {name} {shape} C{C}")
+        form = kata.fwd_form(shape["B"], shape["H"], shape["T"], 64, 64, C, 1, kata.KATA_BF16)
+        log(f"case noalloc vs kata_fwd_chunked {name} {shape} C{C}, form {form}")
+        assert form == (kata.FWD_STATES if shape["T"] > 6144 else kata.FWD_QUADRATIC)
         inp = workloads.make_inputs(name, **shape)
         q, k, v = _dev3(inp, dtype)
         a = kata.fwd_chunked_noalloc(q, k, v, C)
@@ -47,8 +50,10 @@ def test_noalloc_matches_allocating_entry_point(kata, orc):
 
 def test_noalloc_fp32_path_twice(kata, orc):
     import torch
-    for T in (300, 65):
+    for T in (300, 65, 4200):  # quadratic, quadratic, chunk states
         log(f"case noalloc fp32 path tiny_f32 B1 H2 T{T} d16 C32")
+        assert kata.fwd_form(1, 2, T, 16, 16, 32, 1, kata.KATA_F32) == (
+            kata.FWD_STATES if T > 4096 else kata.FWD_QUADRATIC)
         inp = workloads.make_inputs("tiny_f32", T=T)
         q, k, v = _dev3(inp, "f32")
         a = kata.fwd_chunked_noalloc(q, k, v, 32)
