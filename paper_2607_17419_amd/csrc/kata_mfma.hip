@@ -300,12 +300,12 @@ __global__ __launch_bounds__((64 * StateGrid<D, DV, NG>::NW)) void span_state_ke
   const int part = jx % SG::NB;
   // Work item li over the NS - 1 spans per head that enter a prefix (each
   // head's last span is left out).  All of these spans carry the same work, so
-  // the XCD a work item lands on (work item mod 8) needs no balancing.  At
-  // D 64 the order is span-major: the keys and values read last are then those
-  // of the last spans, which the output kernel, starting with them,
-  // still finds in the Infinity Cache: the forward of B1 H16 T131072 takes
-  // 1838 instead of 1865 us, that of B2 H16 T30011 with g 2 615 instead of 627.
-  // At D 32 (B4 H8 T16301) it is 211 instead of 209 us: head by head.
+  // the XCD a work item lands on (work item mod 8) needs no balancing.  At D 64
+  // the order is span-major: this kernel's reads of K and V fall from 681 to 545 MB
+  // at B1 H16 T131072 (537 at least; the output kernel's stay), and that forward
+  // takes 1860-1880 instead of 1897-1909 us, that of B2 H16 T30011 with g 2 617-620
+  // instead of 629-631 (this kernel 210 of them instead of 222).  At D 32 (B4 H8
+  // T16301) it is 211 instead of 209 us: head by head.
   const int li = sp0 + 8 * (jx / SG::NB) + (id & 7);
   if (li >= nsp) return;  // whole workgroup: padding of the grid
   const int s = D == 64 ? li / BH : li % (NS - 1);
