@@ -171,15 +171,16 @@ def test_decode_of_more_heads_than_a_wide_launch_holds(kata):
 @pytest.mark.parametrize("H,T,d,dv,g", [(2, 200, 64, 64, 1), (16, 130, 64, 64, 2), (2, 100, 7, 5, 1),
                                         (1, 100, 64, 256, 1)])
 @pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
-def test_state_non_finite_inputs(kata, H, T, d, dv, g, bad):
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_state_non_finite_inputs(kata, H, T, d, dv, g, bad, dtype):
     """One non-finite entry of v or k gives the infinities and NaN of fp32
     arithmetic in its own state entries, and the sums elsewhere (one wave and four
     per tile, both staging forms)."""
     import torch
     a, b = (torch.from_numpy(x) for x in _pairs(d, g))
     for name in ("v", "k"):
-        log(f"case state {bad} in {name}: H{H} T{T} d{d} dv{dv} g{g}")
-        k, v = _inputs("bf16", H, T, d, dv, 9)
+        log(f"case state {dtype} {bad} in {name}: H{H} T{T} d{d} dv{dv} g{g}")
+        k, v = _inputs(dtype, H, T, d, dv, 9)
         (v if name == "v" else k)[0, H - 1, 70, 3] = bad
         S, z = kata.mg_prefill_state(k.cuda(), v.cuda(), g)
         torch.cuda.synchronize()
